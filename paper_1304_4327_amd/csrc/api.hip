@@ -201,8 +201,19 @@ knn_status search(const knn_tree *ref, const knn_tree *query, int k, const knn_o
                     "lists of at most 16");
 
     const int waves = (nq_leaves + NG - 1) / NG;
-    const int grid = (waves + 3) / 4;
-    const bool use_order = (!bf16 || ref->dp < 64) && waves > 1;
+    const char *wlog_path = arena ? nullptr : std::getenv("KNN_WAVE_LOG");
+    // stride 64: the sweep with two query leaves per wave, for either
+    // precision (it returns what the FP32 walk returns; see walk_ties).  Not
+    // for the no-alloc form (its operands take 4 KB per reference leaf), nor
+    // for a seeded FP32 search, whose second pass runs inside the walk.
+    const bool pair = ref->dp == 64 && !arena && !dbg && max_leaf <= 32 && ref->leaf_slots <= 32 &&
+                      (bf16 || !opts.seed_radius);
+    // the pair sweep: the four waves of a workgroup take one pair of leaves
+    // while that leaves CUs idle otherwise
+    const int split = pair && pair_parts(nq_leaves) ? 1 : 0;
+    const int grid = pair ? pair_grid(nq_leaves, split != 0) : (waves + 3) / 4;
+    const bool use_order =
+        !pair && (!bf16 || ref->dp < 64) && waves > 1;
     if (arena) {
         const size_t need = Scratch::piece(2 * ST_COUNT * sizeof(unsigned long long)) +
                             (opts.seed_radius ? Scratch::piece(size_t(nq_leaves) * 4) +
@@ -248,6 +259,7 @@ knn_status search(const knn_tree *ref, const knn_tree *query, int k, const knn_o
     a.d = ref->d;
     a.k = k;
     a.lpl_log2 = lpl_log2;
+    a.split = split;
     a.bound = opts.bound;
     a.self = opts.exclude_self ? 1 : 0;
     a.seed = opts.seed_radius;
@@ -258,7 +270,6 @@ knn_status search(const knn_tree *ref, const knn_tree *query, int k, const knn_o
     a.fb_bound = fb_bound;
     a.stats = dstats;
     // debug aid: KNN_WAVE_LOG=<file> writes per-wave counters of the main launch
-    const char *wlog_path = arena ? nullptr : std::getenv("KNN_WAVE_LOG");
     uint32_t *wlog = nullptr;
 
     if (dbg) {
@@ -292,10 +303,8 @@ knn_status search(const knn_tree *ref, const knn_tree *query, int k, const knn_o
     } else if (dstats) {
         KNN_HIP(zero_words(dstats, 2 * 2 * ST_COUNT, s));
     }
-    // the d = 64 sweep's wave-independent form: its reference-side operands,
-    // made once per search (not in the no-alloc form, which keeps the staged
-    // sweep: they take 4 KB per reference leaf)
-    if (bf16 && ref->dp == 64 && !arena && !dbg) {
+    if (pair) {  // the reference-side operands, made once per search
+        a.walk_ties = bf16 ? 0 : 1;
         const int nl = int(ref->first_leaf) + 1;
         const size_t pl = size_t((nl + kSweepBlock - 1) / kSweepBlock) * kSweepBlock;  // padded leaves
         uint16_t *abf = nullptr, *cbf = nullptr;
@@ -333,6 +342,7 @@ knn_status search(const knn_tree *ref, const knn_tree *query, int k, const knn_o
         KNN_HIP(hipEventRecord(ev[0], s));
     }
     KNN_HIP(dbg    ? launch_search_valu_debug_d3(a, K, grid, s)
+            : pair ? launch_search_pair_dp64(a, k + (opts.exclude_self ? 1 : 0), s)
             : mt   ? (ref->dp == 16 ? launch_search_mt_d16(a, K, grid, s)
                                     : launch_search_mt_d32(a, K, grid, s))
             : bf16 ? launch_mfma(a, ref->dp, K, grid, s)
@@ -352,7 +362,8 @@ knn_status search(const knn_tree *ref, const knn_tree *query, int k, const knn_o
         b.active = fb_flag;
         b.stats = dstats ? dstats + ST_COUNT : nullptr;  // counted separately
         b.wave_log = nullptr;
-        KNN_HIP(launch_mfma(b, ref->dp, K, grid, s));
+        KNN_HIP(pair ? launch_search_pair_dp64(b, k + (opts.exclude_self ? 1 : 0), s)
+                     : launch_mfma(b, ref->dp, K, grid, s));
     }
     if (timing) KNN_HIP(hipEventRecord(ev[2], s));
     unsigned long long hst[2 * ST_COUNT] = {};

@@ -39,9 +39,11 @@ struct SearchArgs {
     // launch order of the wave slots (largest leaf radius first), or NULL:
     // wave i of the launch takes slot order[i]
     const int *order;
+    int split;  // k_search_pair: the waves of a workgroup share one pair of leaves
     int d, k, lpl_log2;
     int bound;          // knn_bound
     int self;           // exclude reference position == query position
+    int walk_ties;      // k_search_pair: equal k-th distances in the walk's order
     const float *seed;  // per query leaf, or NULL
     int64_t *out_idx;
     float *out_dist;
@@ -53,17 +55,17 @@ struct SearchArgs {
     unsigned long long *stats;  // ST_COUNT counters, or NULL; the FP32 kernel with a
                                 // seed adds its second pass's counts to the next
                                 // ST_COUNT
-    // wave-independent d = 64 sweep (k_search_mfma_sweep with W): the
+    // d = 64 sweep with two query leaves per wave (k_search_pair): the
     // reference side of every tile and block Score, centred on the centre
     // C_B of the leaf's block (subtree of 32 leaves), made once per search
-    // by k_wsweep_prep; sw_abf == NULL selects the staged sweep.  Leaves are
-    // padded to whole blocks.
-    const uint16_t *sw_abf;  // [leaf][32 rows][h][s][8] bf16(-2 (r - C_B)), 0 past the leaf
+    // by k_wsweep_prep.  Leaves are padded to whole blocks.  An operand's 8
+    // dimensions 16 s + 8 h .. of 32 rows are 512 contiguous bytes.
+    const uint16_t *sw_abf;  // [leaf][s][h][32 rows][8] bf16(-2 (r - C_B)), 0 past the leaf
     const float *sw_rn;      // [leaf][32] |r - C_B|^2 (FP32), +inf past the leaf
     const float *sw_rlen;    // [leaf] largest |r - C_B|, rounded up
-    const uint16_t *sw_cbf;  // [leaf][h][s][8] bf16(-2 (C_L - C_B)), C_L the leaf's box centre
+    const uint16_t *sw_cbf;  // [block][s][h][32 leaves][8] bf16(-2 (C_L - C_B)), C_L the leaf's ball centre
     const float *sw_cn;      // [leaf] |C_L - C_B|^2, +inf for empty or padding leaves
-    const float *sw_lam;     // [leaf] lambda of the leaf, 0 for padding
+    const float *sw_lam;     // [leaf] radius of the leaf's ball, 0 for padding
     const float *sw_bcen;    // [block][DP] C_B
     const float *sw_rcb;     // [block] largest |C_L - C_B| of the block, rounded up
     uint32_t *wave_log;         // debug: 8 words per wave (ticks, scores, tiles, inserts, passes, leaf,
@@ -122,6 +124,18 @@ hipError_t launch_search_valu_debug_d3(const SearchArgs &a, int K, int grid, hip
 // when a.seed is set
 hipError_t launch_search_mt_d16(const SearchArgs &a, int K, int grid, hipStream_t s);
 hipError_t launch_search_mt_d32(const SearchArgs &a, int K, int grid, hipStream_t s);
+
+// the d = 64 sweep with two query leaves per wave (search_pair_d64.hip): the
+// operands of launch_wsweep_prep, lists of kk <= 64 entries
+constexpr int kPairLeaves = 8;  // query leaves per workgroup (two per wave)
+// parts: one pair of leaves per workgroup, its four waves dealing the blocks
+inline int pair_grid(int n_leaves, bool parts) {
+    const int per = parts ? 2 : kPairLeaves;
+    return (n_leaves + per - 1) / per;
+}
+// (256 CUs, two workgroups on each)
+inline bool pair_parts(int n_leaves) { return pair_grid(n_leaves, false) <= 256; }
+hipError_t launch_search_pair_dp64(const SearchArgs &a, int kk, hipStream_t s);
 
 // reference leaves the d = 64 sweep scores together (one subtree)
 constexpr int kSweepBlock = 32;

@@ -1,5 +1,5 @@
-// Instantiation of the BF16 MFMA kernel for stride 64 (leaf sweep form), and
-// the reference-side operands of its wave-independent form.
+// Instantiation of the staged BF16 sweep for stride 64 (the no-alloc entry),
+// and the reference-side operands of the sweep with two query leaves per wave.
 #include "search_mfma_sweep.hpp"
 
 namespace knnx {
@@ -35,7 +35,7 @@ __global__ __launch_bounds__(1024) void k_wsweep_prep(const SearchArgs a, uint16
     const int rb = blockIdx.x;
     const int tid = threadIdx.x;
     const int ls = tid >> 8, t = tid & 255;
-    const int i = t >> 3, c = t & 7, h = c & 1, s = c >> 1;
+    const int i = t >> 3, c = t & 7;
     const int nl = a.r_first_leaf + 1;
     const int n_blocks = (nl + NB - 1) / NB;
     const int bnode = n_blocks - 1 + rb;  // heap index of the block's subtree node
@@ -68,7 +68,7 @@ __global__ __launch_bounds__(1024) void k_wsweep_prep(const SearchArgs a, uint16
                 n2 = fmaf(df, df, n2);
                 out[e] = (__bf16)(-2.0f * df);
             }
-            *reinterpret_cast<bf16x8_t *>(abf + (int64_t(L) * NB + i) * DP + h * (DP / 2) + s * 8) = out;
+            *reinterpret_cast<bf16x8_t *>(abf + int64_t(L) * NB * DP + (c * NB + i) * 8) = out;
             n2 = reduce8(n2, OpAdd());  // the row's whole norm, in all 8 lanes
             if (c == 0) {
                 rn[int64_t(L) * NB + i] = vr ? n2 : kInf;
@@ -120,8 +120,7 @@ __global__ __launch_bounds__(1024) void k_wsweep_prep(const SearchArgs a, uint16
                 asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
             }
             const float df = has ? best_c - s_cb[t] : 0.f;
-            const int ps = t >> 4, ph = (t >> 3) & 1, pe = t & 7;
-            cbf[int64_t(L) * DP + ph * (DP / 2) + ps * 8 + pe] =
+            cbf[int64_t(rb) * NB * DP + ((t >> 3) * NB + l0 + ls) * 8 + (t & 7)] =
                 __builtin_bit_cast(uint16_t, (__bf16)(-2.0f * df));
             const float c2 = reduce64(df * df, OpAdd());
             if (t == 0) {

@@ -60,6 +60,8 @@
 // beats min(D_p[k], B); candidates are re-scored in FP64 before they may
 // enter the list, so the lists are those of the FP32 form.
 
+#pragma once
+
 #include "bf16_tile.hpp"
 #include "search.hpp"
 

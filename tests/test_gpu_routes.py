@@ -1,0 +1,60 @@
+"""The kernels that serve a call beside the slot-per-wave walk return what the
+walk returns, ties at the k-th place included: one query per wave (few
+queries, d <= 16) against the walk that a call with counters takes, and the
+FP32 sweep at d > 32 against the no-alloc entry's walk.  Bit for bit: the
+distances are the same numbers and every tie follows the walk's order."""
+import numpy as np
+import pytest
+
+from oracle import knn as ok
+from oracle import parity
+from paper_1304_4327_amd import datagen
+
+pytestmark = pytest.mark.gpu
+
+
+def _points(kind, n, d, seed):
+    rng = np.random.default_rng(seed)
+    if kind == "lattice":  # many equal distances
+        return rng.integers(0, max(2, round(n ** (1.0 / d))), (n, d)).astype(np.float32)
+    x = (rng.standard_normal((n, d)) * rng.uniform(0.2, 3.0, d)).astype(np.float32)
+    if kind == "twice":    # every point two times: ties in pairs
+        x[n // 2:2 * (n // 2)] = x[:n // 2]
+    return x
+
+
+def _trees(ref, q, leaf):
+    import torch
+    from paper_1304_4327_amd import knn
+    rt = knn.knn_build_tree(torch.from_numpy(ref).cuda(), leaf)
+    return rt, None if q is None else knn.knn_build_tree(torch.from_numpy(q).cuda(), leaf)
+
+
+@pytest.mark.parametrize("n_ref,n_q,leaf,k", [(40, 5, 32, 7), (900, 70, 16, 1), (5000, 400, 32, 50),
+                                              (5000, 900, 20, 62), (3000, 0, 32, 16),
+                                              (2100, 66_000, 32, 8)])
+@pytest.mark.parametrize("d,kind", [(33, "random"), (64, "twice")])
+def test_fp32_sweep_equals_the_walk(n_ref, n_q, leaf, k, d, kind):
+    """The FP32 sweep (parts of a workgroup and whole workgroups) against the
+    walk of the no-alloc entry, and against the oracle."""
+    import torch
+    from paper_1304_4327_amd import knn
+    ref = _points(kind, n_ref, d, n_ref)
+    q = _points(kind, n_q, d, 7) if n_q else None
+    if q is not None and kind == "twice":
+        m = min(n_q, n_ref) // 2
+        q[:m] = ref[:m]
+    rt, qt = _trees(ref, q, leaf)
+    nq = n_q or n_ref
+    print(f"pair: n_ref={n_ref} n_q={n_q} d={d} k={k} leaf={leaf} {kind}", flush=True)
+    got = knn.knn_search(rt, qt, k, exclude_self=q is None)
+    out = (torch.empty((nq, k), dtype=torch.int64, device="cuda"),
+           torch.empty((nq, k), dtype=torch.float32, device="cuda"))
+    want = knn.knn_search_noalloc(rt, qt, k, out, exclude_self=q is None)
+    torch.cuda.synchronize()
+    assert torch.equal(got[1], want[1]) and torch.equal(got[0], want[0])
+    if kind == "random":
+        rows = np.arange(0, nq, max(1, nq // 200))
+        x = ref if q is None else q
+        oi, od = ok.knn_rows(x, rows, ref, k, exclude_self=q is None)
+        parity.assert_ok(x, ref, k, got[0].cpu().numpy(), got[1].cpu().numpy(), oi, od, rows=rows)
