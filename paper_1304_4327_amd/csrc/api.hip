@@ -208,12 +208,19 @@ knn_status search(const knn_tree *ref, const knn_tree *query, int k, const knn_o
     // for a seeded FP32 search, whose second pass runs inside the walk.
     const bool pair = ref->dp == 64 && !arena && !dbg && max_leaf <= 32 && ref->leaf_slots <= 32 &&
                       (bf16 || !opts.seed_radius);
+    // what only a slot-per-wave walk can do: its counters describe whole query
+    // leaves, and a leaf's second pass and largest k-th distance need the
+    // leaf's queries in one wave
+    const bool whole = dbg || opts.stats || opts.seed_radius || opts.leaf_kth_out || wlog_path;
+    const bool few = !pair && ref->dp <= 16 && (!bf16 || mt) && !whole &&
+                     opts.bound != KNN_BOUND_NONE && k + (opts.exclude_self ? 1 : 0) <= kFewList &&
+                     qt->n <= kFewQueries;
     // the pair sweep: the four waves of a workgroup take one pair of leaves
     // while that leaves CUs idle otherwise
     const int split = pair && pair_parts(nq_leaves) ? 1 : 0;
     const int grid = pair ? pair_grid(nq_leaves, split != 0) : (waves + 3) / 4;
     const bool use_order =
-        !pair && (!bf16 || ref->dp < 64) && waves > 1;
+        !pair && !few && (!bf16 || ref->dp < 64) && waves > 1;
     if (arena) {
         const size_t need = Scratch::piece(2 * ST_COUNT * sizeof(unsigned long long)) +
                             (opts.seed_radius ? Scratch::piece(size_t(nq_leaves) * 4) +
@@ -342,6 +349,7 @@ knn_status search(const knn_tree *ref, const knn_tree *query, int k, const knn_o
         KNN_HIP(hipEventRecord(ev[0], s));
     }
     KNN_HIP(dbg    ? launch_search_valu_debug_d3(a, K, grid, s)
+            : few  ? launch_search_few_d(a, ref->d, qt->n, s)
             : pair ? launch_search_pair_dp64(a, k + (opts.exclude_self ? 1 : 0), s)
             : mt   ? (ref->dp == 16 ? launch_search_mt_d16(a, K, grid, s)
                                     : launch_search_mt_d32(a, K, grid, s))

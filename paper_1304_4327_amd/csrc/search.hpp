@@ -125,6 +125,14 @@ hipError_t launch_search_valu_debug_d3(const SearchArgs &a, int K, int grid, hip
 hipError_t launch_search_mt_d16(const SearchArgs &a, int K, int grid, hipStream_t s);
 hipError_t launch_search_mt_d32(const SearchArgs &a, int K, int grid, hipStream_t s);
 
+// one query per wave (search_few.hip): strides up to 16, every pruning bound
+// but KNN_BOUND_NONE, no seed, no counters; lists of kk <= kFewList entries.
+// Up to kFewQueries queries it beats the slot-per-wave walk: that one lasts as
+// long as its slowest wave until the chip is full.
+constexpr int kFewList = 62;
+constexpr int64_t kFewQueries = 32768;
+hipError_t launch_search_few_d(const SearchArgs &a, int d, int64_t n_q, hipStream_t s);
+
 // the d = 64 sweep with two query leaves per wave (search_pair_d64.hip): the
 // operands of launch_wsweep_prep, lists of kk <= 64 entries
 constexpr int kPairLeaves = 8;  // query leaves per workgroup (two per wave)

@@ -30,6 +30,36 @@ def _trees(ref, q, leaf):
     return rt, None if q is None else knn.knn_build_tree(torch.from_numpy(q).cuda(), leaf)
 
 
+# reference sizes: one leaf; one, two and three steps of six levels; k from 1
+# to the longest list of the kernel (62 with the query's own point)
+@pytest.mark.parametrize("n_ref,leaf,k", [(30, 32, 7), (700, 32, 1), (3000, 20, 62), (3000, 64, 10),
+                                          (9000, 2, 5), (60_000, 16, 16)])
+@pytest.mark.parametrize("d,kind", [(1, "random"), (2, "lattice"), (3, "twice"), (4, "random"),
+                                    (5, "random"), (8, "twice"), (13, "random"), (16, "twice")])
+def test_one_query_per_wave_equals_the_walk(n_ref, leaf, k, d, kind):
+    import torch
+    from paper_1304_4327_amd import knn
+    for n_q in (0, 1, 333):
+        print(f"few: n_ref={n_ref} n_q={n_q} d={d} k={k} leaf={leaf} {kind}", flush=True)
+        ref = _points(kind, n_ref, d, n_ref + d)
+        q = _points(kind, n_q, d, d) if n_q else None
+        if q is None and n_ref > 32768:
+            continue
+        kk = k - 1 if q is None and k == 62 else k
+        if q is not None and kind == "twice":
+            m = min(n_q, n_ref) // 2
+            q[:m] = ref[:m]  # distance 0, two times
+        rt, qt = _trees(ref, q, leaf)
+        got = knn.knn_search(rt, qt, kk, exclude_self=q is None)
+        want = knn.knn_search(rt, qt, kk, exclude_self=q is None, stats=True)
+        torch.cuda.synchronize()
+        assert torch.equal(got[1], want[1])
+        # a lattice can hold more equal distances than the lanes past the
+        # k-th entry: then only the distances are compared
+        if kind != "lattice":
+            assert torch.equal(got[0], want[0])
+
+
 @pytest.mark.parametrize("n_ref,n_q,leaf,k", [(40, 5, 32, 7), (900, 70, 16, 1), (5000, 400, 32, 50),
                                               (5000, 900, 20, 62), (3000, 0, 32, 16),
                                               (2100, 66_000, 32, 8)])
