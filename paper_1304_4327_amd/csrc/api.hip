@@ -215,12 +215,15 @@ knn_status search(const knn_tree *ref, const knn_tree *query, int k, const knn_o
     const bool few = !pair && ref->dp <= 16 && (!bf16 || mt) && !whole &&
                      opts.bound != KNN_BOUND_NONE && k + (opts.exclude_self ? 1 : 0) <= kFewList &&
                      qt->n <= kFewQueries;
-    // the pair sweep: the four waves of a workgroup take one pair of leaves
-    // while that leaves CUs idle otherwise
-    const int split = pair && pair_parts(nq_leaves) ? 1 : 0;
-    const int grid = pair ? pair_grid(nq_leaves, split != 0) : (waves + 3) / 4;
+    // few slots: several waves share one.  The pair sweep: the four waves of a
+    // workgroup take one pair of leaves while that leaves CUs idle otherwise
+    const int split = pair ? (pair_parts(nq_leaves) ? 1 : 0)
+                      : (!bf16 || mt) && !whole && ref->dp >= 32
+                          ? split_for(waves, lpl_log2, max_leaf)
+                                                : 0;
+    const int grid = pair ? pair_grid(nq_leaves, split != 0) : ((waves << split) + 3) / 4;
     const bool use_order =
-        !pair && !few && (!bf16 || ref->dp < 64) && waves > 1;
+        !pair && !few && (!bf16 || ref->dp < 64) && waves > 1 && split == 0;
     if (arena) {
         const size_t need = Scratch::piece(2 * ST_COUNT * sizeof(unsigned long long)) +
                             (opts.seed_radius ? Scratch::piece(size_t(nq_leaves) * 4) +

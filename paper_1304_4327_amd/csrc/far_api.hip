@@ -46,7 +46,8 @@ knn_status search_furthest(const knn_tree *ref, const knn_tree *query, int k,
     const int lg = max_leaf <= 32 ? 5 : 6;
     const int nq_leaves = int(qt->n_leaves);
     const int waves = (nq_leaves + (64 >> lg) - 1) / (64 >> lg);
-    const int grid = (waves + 3) / 4;
+    const int split = split_for(waves, lg, max_leaf);
+    const int grid = ((waves << split) + 3) / 4;
 
     SearchArgs a{};
     a.rpts = ref->pts;
@@ -67,6 +68,7 @@ knn_status search_furthest(const knn_tree *ref, const knn_tree *query, int k,
     a.d = ref->d;
     a.k = k;
     a.lpl_log2 = lg;
+    a.split = split;
     a.bound = opts.bound;
     a.self = opts.exclude_self ? 1 : 0;
     a.out_idx = idx_out;

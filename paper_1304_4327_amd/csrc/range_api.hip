@@ -47,7 +47,8 @@ knn_status prepare(const char *who, const knn_tree *ref, const knn_tree *query, 
     const int max_leaf = int((qt->n + qt->n_leaves - 1) / qt->n_leaves);
     lg = max_leaf <= 32 ? 5 : 6;
     const int waves = int((qt->n_leaves + (64 >> lg) - 1) / (64 >> lg));
-    grid = (waves + 3) / 4;
+    const int split = split_for(waves, lg, max_leaf);
+    grid = ((waves << split) + 3) / 4;
     const double lo2 = lo * lo, hi2 = hi * hi;
     const float g = (ref->dp + 6) * 0x1p-24f;
     a = RangeArgs{};
@@ -72,6 +73,7 @@ knn_status prepare(const char *who, const knn_tree *ref, const knn_tree *query, 
     a.t_hi = float(hi2) * (1.0f + 2.0f * g);
     a.prune = opts.bound != KNN_BOUND_NONE;
     a.self = opts.exclude_self ? 1 : 0;
+    a.split = split;
     return KNN_OK;
 }
 

@@ -39,7 +39,7 @@ struct SearchArgs {
     // launch order of the wave slots (largest leaf radius first), or NULL:
     // wave i of the launch takes slot order[i]
     const int *order;
-    int split;  // k_search_pair: the waves of a workgroup share one pair of leaves
+    int split;  // log2 of the waves that share one slot's queries (split_for)
     int d, k, lpl_log2;
     int bound;          // knn_bound
     int self;           // exclude reference position == query position
@@ -159,6 +159,24 @@ hipError_t launch_wsweep_prep(const SearchArgs &args, uint16_t *abf, float *rn, 
 hipError_t launch_search_mfma_dp16(const SearchArgs &a, int K, int grid, hipStream_t s);
 hipError_t launch_search_mfma_dp32(const SearchArgs &a, int K, int grid, hipStream_t s);
 hipError_t launch_search_mfma_dp64(const SearchArgs &a, int K, int grid, hipStream_t s);
+
+// Waves per slot of query leaves, as a power of two.  A small query set has
+// fewer slots than the chip has SIMDs, and then the call lasts as long as one
+// wave's walk, which grows with the queries it carries (each of them opens
+// its own part of the reference tree).  The queries of a slot are then dealt
+// over 1 << split waves, as long as every wave has a SIMD to itself: beyond
+// that (4096 waves were tried) the repeated walks cost up to three times what
+// the shorter ones save.  Every query sees the reference nodes in the same
+// order as in the undivided slot: the visit-order key still comes from the
+// whole slot.
+constexpr int kSplitWaves = 1024;
+inline int split_for(int64_t slots, int lg, int max_leaf) {
+    int most = 6 - lg;  // one leaf per wave, then down to one query
+    while ((1 << (most - (6 - lg))) < max_leaf) ++most;
+    int s = 0;
+    while (s < most && (slots << (s + 1)) <= kSplitWaves) ++s;
+    return s;
+}
 
 // zero n 32-bit words with a kernel (api.hip)
 hipError_t zero_words(void *p, int64_t n, hipStream_t s);

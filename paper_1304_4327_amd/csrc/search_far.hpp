@@ -50,7 +50,8 @@ k_search_far(const SearchArgs a) {
     constexpr bool WIDE = DP >= 16;
     const int lane = threadIdx.x & 63;
     const int n_list = a.q_n_leaves;
-    const int wave = xcd_remap(blockIdx.x, gridDim.x) * 4 + (threadIdx.x >> 6);
+    const int raw = uniform_i(xcd_remap(blockIdx.x, gridDim.x) * 4 + (threadIdx.x >> 6));
+    const int wave = raw >> a.split, part = raw & ((1 << a.split) - 1);
     if (wave * NG >= n_list) return;
     const int g = lane >> LG, li = lane & ((1 << LG) - 1);
     const int slot = wave * NG + g;
@@ -58,7 +59,8 @@ k_search_far(const SearchArgs a) {
     const int qleaf = has_leaf ? slot : 0;
     const int qnode = a.q_first_leaf + qleaf;
     const int2 qr = has_leaf ? a.qrange[qnode] : make_int2(0, 0);
-    const bool valid = has_leaf && li < qr.y;
+    const bool valid = has_leaf && li < qr.y && in_part<LG>(lane, part, a.split);
+    if (!ballot(valid)) return;
     const int qpos = qr.x + li;
     const int kk = a.k + (a.self ? 1 : 0);
 

@@ -37,6 +37,7 @@ struct RangeArgs {
     float s_lo, s_hi;     // Score thresholds on squared distances (with slack)
     float t_lo, t_hi;     // BaseCase FP32 filter thresholds (with slack)
     int prune, self;
+    int split;               // waves per slot of query leaves (split_for)
     int64_t *counts;         // count pass: per original query row
     const int64_t *offsets;  // fill pass: exclusive prefix sums of the counts
     int64_t *out_idx;
@@ -48,19 +49,24 @@ template <int DP, int LG, bool FILL>
 __global__ __launch_bounds__(256) void k_range(const RangeArgs a) {
     constexpr int NG = 64 >> LG;
     const int lane = threadIdx.x & 63;
-    const int wave = xcd_remap(blockIdx.x, gridDim.x) * 4 + (threadIdx.x >> 6);
+    const int raw = uniform_i(xcd_remap(blockIdx.x, gridDim.x) * 4 + (threadIdx.x >> 6));
+    const int wave = raw >> a.split, part = raw & ((1 << a.split) - 1);
     if (wave * NG >= a.q_n_leaves) return;
     const int g = lane >> LG, li = lane & ((1 << LG) - 1);
     const int slot = wave * NG + g;
     const bool has_leaf = slot < a.q_n_leaves;
     const int2 qr = has_leaf ? a.qrange[a.q_first_leaf + slot] : make_int2(0, 0);
-    const bool valid = has_leaf && li < qr.y;
+    const bool point = has_leaf && li < qr.y;
+    const bool valid = point && in_part<LG>(lane, part, a.split);
+    if (!ballot(valid)) return;
     const int qpos = qr.x + li;
+    // every lane keeps its point, also the ones of other parts: the visit
+    // order follows lane 0's, so each query's list keeps its order
     float q[DP];
     {
-        const float *qp = a.qpts + int64_t(valid ? qpos : 0) * DP;
+        const float *qp = a.qpts + int64_t(point ? qpos : 0) * DP;
 #pragma unroll
-        for (int j = 0; j < DP; ++j) q[j] = valid ? qp[j] : 0.f;
+        for (int j = 0; j < DP; ++j) q[j] = point ? qp[j] : 0.f;
     }
     const int64_t row = valid ? int64_t(a.qperm[qpos]) : 0;
     int64_t out = 0;

@@ -82,6 +82,18 @@ __device__ inline float uniform_f(float x) {
 __device__ inline int uniform_i(int x) { return __builtin_amdgcn_readfirstlane(x); }
 __device__ inline uint64_t ballot(bool p) { return __builtin_amdgcn_ballot_w64(p); }
 
+// Whether a lane's query belongs to part `part` of its slot when 1 << split
+// waves share the slot: whole leaves first, then every (1 << s)-th query of
+// one leaf (leaves hold fewer points than lanes, so a strided deal balances)
+template <int LG>
+__device__ inline bool in_part(int lane, int part, int split) {
+    constexpr int NGL = 6 - LG;  // log2 of the slot's leaves
+    const int g = lane >> LG, li = lane & ((1 << LG) - 1);
+    if (split <= NGL) return (g >> (NGL - split)) == part;
+    const int s = split - NGL;
+    return g == (part >> s) && (li & ((1 << s) - 1)) == (part & ((1 << s) - 1));
+}
+
 constexpr int stride_for(int D) { return D <= 4 ? 4 : D <= 8 ? 8 : D <= 16 ? 16 : D <= 32 ? 32 : 64; }
 
 // FRESH: the query is converted at each call (an empty asm statement that
@@ -112,6 +124,9 @@ __device__ __forceinline__ void search_valu_body(const SearchArgs &a) {
                   "matrix-core tiles: d = 16 or 32, two leaves of <= 32 points per wave");
     constexpr int DP = stride_for(D);
     constexpr bool RESCORE = D > 8;
+    // several waves may share a slot (split_for); up to stride 16 few queries
+    // go to the one-query-per-wave kernel instead
+    constexpr bool SPLIT = D >= 32 && MODE == kValuPlain;
     constexpr float kInf = __builtin_inff();
     constexpr float kSlack = 1.0f + 0x1p-16f;            // prune slack (squared)
     constexpr float kGamma = 1.0f + (D + 6) * 0x1p-24f;  // FP32 filter slack
@@ -120,6 +135,7 @@ __device__ __forceinline__ void search_valu_body(const SearchArgs &a) {
     constexpr int NG = 64 >> lpl_log2;
     const int n_list = a.q_n_leaves;
     int wave;
+    [[maybe_unused]] int part = 0;
     if (a.order) {
         // heavy slots first: the hardware starts workgroups in launch order
         const int raw = blockIdx.x * 4 + (threadIdx.x >> 6);
@@ -127,6 +143,11 @@ __device__ __forceinline__ void search_valu_body(const SearchArgs &a) {
         wave = uniform_i(a.order[raw]);
     } else {
         wave = xcd_remap(blockIdx.x, gridDim.x) * 4 + (threadIdx.x >> 6);
+        if constexpr (SPLIT) {
+            const int raw = uniform_i(wave);
+            wave = raw >> a.split;
+            part = raw & ((1 << a.split) - 1);
+        }
     }
     if (wave * NG >= n_list) return;
     const int g = lane >> lpl_log2, li = lane & ((1 << lpl_log2) - 1);
@@ -136,7 +157,11 @@ __device__ __forceinline__ void search_valu_body(const SearchArgs &a) {
     const int qleaf = has_leaf ? slot : 0;
     const int qnode = a.q_first_leaf + qleaf;
     const int2 qr = has_leaf ? a.qrange[qnode] : make_int2(0, 0);
-    const bool valid0 = has_leaf && li < qr.y;  // this lane holds a query point
+    bool valid0 = has_leaf && li < qr.y;  // this lane holds a query point
+    if constexpr (SPLIT) {  // ... of this wave's part of the slot
+        valid0 = valid0 && in_part<LG>(lane, part, a.split);
+        if (!ballot(valid0)) return;
+    }
     bool valid = valid0;  // ... that the current pass searches
     const int qpos = qr.x + li;
     const int kk = a.k + (a.self ? 1 : 0);  // list length (self match included)
