@@ -28,6 +28,21 @@
 
 namespace knnx {
 
+// minimum over the wave (wave-uniform result), lane moves by DPP alone: rows
+// of 16, then each row's last lane to the next row, then to the upper half
+__device__ inline float wave_min(float v) {
+    v = reduce16(v, OpMin());
+    const int a = __builtin_bit_cast(int, v);
+    v = fminf(v, __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(a, a, 0x142, 0xA, 0xF, false)));
+    const int b = __builtin_bit_cast(int, v);
+    v = fminf(v, __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(b, b, 0x143, 0xC, 0xF, false)));
+    return __int_as_float(__builtin_amdgcn_readlane(__builtin_bit_cast(int, v), 63));
+}
+// lane l's value from lane l - 1; lane 0 gets `first`
+__device__ inline int lane_before(int v, int first) {
+    return __builtin_amdgcn_update_dpp(first, v, 0x138, 0xF, 0xF, false);
+}
+
 template <int D>
 __global__ __launch_bounds__(256) void k_search_few(const SearchArgs a) {
     constexpr int DP = stride_for(D);
@@ -71,13 +86,12 @@ __global__ __launch_bounds__(256) void k_search_few(const SearchArgs a) {
                 const float nv = at(v, c);
                 if (!(nv <= kth)) continue;
                 const int np = __builtin_amdgcn_readlane(p, c);
-                const float xp = __shfl_up(x, 1);
-                const int ip = __shfl_up(id, 1);
-                const bool shift = lane > 0 && xp > nv;
-                if (x > nv) {
-                    x = shift ? xp : nv;
-                    id = shift ? ip : np;
-                }
+                // entries above the new one move up a lane
+                const float xp = __int_as_float(lane_before(__float_as_int(x), 0xff800000));
+                const int ip = lane_before(id, -1);
+                const bool above = x > nv, shift = xp > nv;
+                x = above ? (shift ? xp : nv) : x;
+                id = above ? (shift ? ip : np) : id;
                 kth = at(x, kk - 1);
             }
             return;
@@ -157,7 +171,7 @@ __global__ __launch_bounds__(256) void k_search_few(const SearchArgs a) {
     };
     // the nearest unvisited node of a step's 64, or -1 when none is in reach
     auto pick = [&](float &d) -> int {
-        const float m = uniform_f(reduce64(d, OpMin()));
+        const float m = wave_min(d);
         if (!(m < kInf) || m > kth * kSlack) return -1;
         const int l = __builtin_ctzll(ballot(d == m));
         if (lane == l) d = kInf;
