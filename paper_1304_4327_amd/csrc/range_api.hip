@@ -2,6 +2,7 @@
 // pass, an exclusive scan of the counts into offsets, the fill pass.
 #include "search_range.hpp"
 
+#include <algorithm>
 #include <cmath>
 #include <string>
 
@@ -69,8 +70,13 @@ knn_status prepare(const char *who, const knn_tree *ref, const knn_tree *query, 
     a.hi2 = hi2;
     a.s_lo = float(lo2) * (1.0f - 0x1p-16f);
     a.s_hi = float(hi2) * (1.0f + 0x1p-16f);
+    // (t_hi is compared strictly, and is never so small that the difference
+    // would lose its sign)
     a.t_lo = float(lo2) * (1.0f - 2.0f * g);
-    a.t_hi = float(hi2) * (1.0f + 2.0f * g);
+    a.t_hi = std::max(std::nextafter(float(hi2) * (1.0f + 2.0f * g), INFINITY), 0x1p-120f);
+    a.in_lo = lo2 > 0.0 ? std::max(float(lo2) * (1.0f + 2.0f * g), 0x1p-120f) : 0.0f;
+    a.in_hi = hi2 < 0x1p-100 ? 0.0f : float(hi2) * (1.0f - 2.0f * g);
+    a.wide = hi2 > 1e38;
     a.prune = opts.bound != KNN_BOUND_NONE;
     a.self = opts.exclude_self ? 1 : 0;
     a.split = split;

@@ -35,7 +35,11 @@ struct RangeArgs {
     int q_first_leaf, q_n_leaves;
     double lo2, hi2;      // exact decision
     float s_lo, s_hi;     // Score thresholds on squared distances (with slack)
-    float t_lo, t_hi;     // BaseCase FP32 filter thresholds (with slack)
+    // BaseCase FP32 filter: a pair outside [t_lo, t_hi) is out of range, one
+    // inside [in_lo, in_hi] in range; FP64 decides between them
+    // (in_lo == 0: no lower limit; wide: FP32 may overflow, FP64 decides all)
+    float t_lo, t_hi, in_lo, in_hi;
+    int wide;
     int prune, self;
     int split;               // waves per slot of query leaves (split_for)
     int64_t *counts;         // count pass: per original query row
@@ -86,6 +90,7 @@ __global__ __launch_bounds__(256) void k_range(const RangeArgs a) {
         const bool keep = valid && (!a.prune || (!(dmin2 > a.s_hi) && !(dmax2 < a.s_lo)));
         return ballot(keep) != 0;
     };
+    // (slots of a leaf are a multiple of 8: whole batches stay inside it)
     constexpr int CH = DP >= 32 ? 1 : 32 / DP;
     auto leaf = [&](int node) {
         ++n_tiles;
@@ -94,35 +99,58 @@ __global__ __launch_bounds__(256) void k_range(const RangeArgs a) {
         const int cnt = uniform_i(rr.y);
         const float *rp = a.rlpts + int64_t(node - a.r_first_leaf) * a.r_leaf_slots * DP;
         n_pairs += uint64_t(cnt) * uint64_t(n_valid);
-        for (int t0 = 0; t0 < cnt; t0 += CH) {
-            // a batch of distances first, one wave-wide test: most batches
-            // hold no candidate for any lane
-            bool cand[CH];
-            uint64_t any = 0;
+        // 32 slots at a time into one bit per pair (the sign of the squared
+        // distance minus a threshold, shifted in), then one survivor per lane
+        // and round: a leaf costs as many rounds as its busiest lane has
+        // survivors, not one for every slot that some lane keeps (1M x 1M, d =
+        // 3, r = 0.2: 77 hits a leaf and wave over 32 slots).  The count pass
+        // adds the pairs that are in range beyond rounding and decides only
+        // the others in FP64.
+        for (int r0 = 0; r0 < cnt; r0 += 32) {
+            const int r1 = min(cnt, r0 + 32);
+            uint32_t hi = 0, lo = 0, in_hi = 0, in_lo = 0;  // bit k: the k-th slot from the end
+            for (int t0 = r0; t0 < r1; t0 += CH) {
 #pragma unroll
-            for (int c = 0; c < CH; ++c) {
-                float sd = 0.f;
+                for (int c = 0; c < CH; ++c) {
+                    float sd = 0.f;
 #pragma unroll
-                for (int j = 0; j < DP; ++j) {
-                    const float df = q[j] - rp[(t0 + c) * DP + j];
-                    sd = fmaf(df, df, sd);
-                }
-                cand[c] = valid && t0 + c < cnt && sd >= a.t_lo && sd <= a.t_hi;
-                any |= ballot(cand[c]);
-            }
-            if (!any) continue;
-#pragma unroll
-            for (int c = 0; c < CH; ++c) {
-                if (cand[c]) {
-                    const double x = d2_fp64_unfused<DP>(q, rp + (t0 + c) * DP);
-                    const int pos = base + t0 + c;
-                    if (x >= a.lo2 && x <= a.hi2 && !(a.self && pos == qpos)) {
-                        if constexpr (FILL) {
-                            a.out_idx[out + found] = a.rperm[pos];
-                            a.out_dist[out + found] = (float)sqrt(x);
-                        }
-                        ++found;
+                    for (int j = 0; j < DP; ++j) {
+                        const float df = q[j] - rp[(t0 + c) * DP + j];
+                        sd = fmaf(df, df, sd);
                     }
+                    auto shift_in = [](uint32_t m, float v) {
+                        return __builtin_amdgcn_alignbit(m, __float_as_uint(v), 31);
+                    };
+                    hi = shift_in(hi, sd - a.t_hi);
+                    if constexpr (!FILL) in_hi = shift_in(in_hi, sd - a.in_hi);
+                    if (a.in_lo > 0.f) {  // uniform
+                        lo = shift_in(lo, sd - a.t_lo);
+                        if constexpr (!FILL) in_lo = shift_in(in_lo, sd - a.in_lo);
+                    }
+                }
+            }
+            // bit k: slot r0 + k (batches may reach past r1: those bits go)
+            const int done = (r1 - r0 + CH - 1) / CH * CH;
+            auto align = [&](uint32_t m) { return __brev(m) >> (32 - done); };
+            const uint32_t rows = r1 - r0 >= 32 ? ~0u : (1u << (r1 - r0)) - 1u;
+            uint32_t m = !valid ? 0u : a.wide ? rows : align(hi & ~lo) & rows;
+            if (a.self && qpos - base - r0 >= 0 && qpos - base - r0 < 32) m &= ~(1u << (qpos - base - r0));
+            if constexpr (!FILL) {
+                const uint32_t sure = a.wide ? 0u : m & align(in_hi & ~in_lo);
+                found += __popc(sure);
+                m &= ~sure;
+            }
+            while (ballot(m != 0)) {
+                const bool has = m != 0;
+                const int t = r0 + (has ? __builtin_ctz(m) : 0);
+                m &= m - 1u;
+                const double x = d2_fp64_unfused<DP>(q, rp + t * DP);
+                if (has && x >= a.lo2 && x <= a.hi2) {
+                    if constexpr (FILL) {
+                        a.out_idx[out + found] = a.rperm[base + t];
+                        a.out_dist[out + found] = (float)sqrt(x);
+                    }
+                    ++found;
                 }
             }
         }
