@@ -7,13 +7,13 @@
 namespace knnx {
 namespace {
 
-hipError_t launch_far(const SearchArgs &a, int dp, int K, int grid, hipStream_t s) {
+hipError_t launch_far(const SearchArgs &a, int dp, int kk, int grid, hipStream_t s) {
     switch (dp) {
-        case 4: return launch_search_far_dp4(a, K, grid, s);
-        case 8: return launch_search_far_dp8(a, K, grid, s);
-        case 16: return launch_search_far_dp16(a, K, grid, s);
-        case 32: return launch_search_far_dp32(a, K, grid, s);
-        default: return launch_search_far_dp64(a, K, grid, s);
+        case 4: return launch_search_far_dp4(a, kk, grid, s);
+        case 8: return launch_search_far_dp8(a, kk, grid, s);
+        case 16: return launch_search_far_dp16(a, kk, grid, s);
+        case 32: return launch_search_far_dp32(a, kk, grid, s);
+        default: return launch_search_far_dp64(a, kk, grid, s);
     }
 }
 
@@ -41,7 +41,6 @@ knn_status search_furthest(const knn_tree *ref, const knn_tree *query, int k,
         return fail(KNN_E_UNSUPPORTED,
                     std::string(who) + ": FP32 only, without seed radius or leaf k-th output");
     const int kk = k + (opts.exclude_self ? 1 : 0);
-    const int K = kk <= 8 ? 8 : kk <= 16 ? 16 : kk <= 32 ? 32 : 64;
     const int max_leaf = int((qt->n + qt->n_leaves - 1) / qt->n_leaves);
     const int lg = max_leaf <= 32 ? 5 : 6;
     const int nq_leaves = int(qt->n_leaves);
@@ -94,7 +93,7 @@ knn_status search_furthest(const knn_tree *ref, const knn_tree *query, int k,
         for (auto &e : ev) KNN_HIP(hipEventCreate(&e));
         KNN_HIP(hipEventRecord(ev[0], s));
     }
-    KNN_HIP(launch_far(a, ref->dp, K, grid, s));
+    KNN_HIP(launch_far(a, ref->dp, kk, grid, s));
     unsigned long long hst[ST_COUNT] = {};
     if (opts.stats) {
         KNN_HIP(hipEventRecord(ev[1], s));

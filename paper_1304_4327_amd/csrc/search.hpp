@@ -189,12 +189,12 @@ hipError_t exclusive_scan(const int64_t *in, int64_t n, int64_t *out, int64_t *t
                           hipStream_t s);
 
 // k-furthest-neighbour kernels (search_far_d*.hip), stride 4 .. 64, lists of
-// 8, 16, 32 or 64
-hipError_t launch_search_far_dp4(const SearchArgs &a, int K, int grid, hipStream_t s);
-hipError_t launch_search_far_dp8(const SearchArgs &a, int K, int grid, hipStream_t s);
-hipError_t launch_search_far_dp16(const SearchArgs &a, int K, int grid, hipStream_t s);
-hipError_t launch_search_far_dp32(const SearchArgs &a, int K, int grid, hipStream_t s);
-hipError_t launch_search_far_dp64(const SearchArgs &a, int K, int grid, hipStream_t s);
+// kk <= 64 entries
+hipError_t launch_search_far_dp4(const SearchArgs &a, int kk, int grid, hipStream_t s);
+hipError_t launch_search_far_dp8(const SearchArgs &a, int kk, int grid, hipStream_t s);
+hipError_t launch_search_far_dp16(const SearchArgs &a, int kk, int grid, hipStream_t s);
+hipError_t launch_search_far_dp32(const SearchArgs &a, int kk, int grid, hipStream_t s);
+hipError_t launch_search_far_dp64(const SearchArgs &a, int kk, int grid, hipStream_t s);
 
 // compile-time list lengths; a request for a list of kk entries (k, or k+1
 // when the query's own point shares the list) uses the smallest K >= kk

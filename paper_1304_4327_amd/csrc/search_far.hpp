@@ -320,15 +320,22 @@ hipError_t launch_search_far_k(const SearchArgs &a, int grid, hipStream_t s) {
     return hipGetLastError();
 }
 
+// list lengths: the smallest that holds kk entries (an insertion costs four
+// instructions a slot)
 template <int DP>
-hipError_t launch_search_far(const SearchArgs &a, int K, int grid, hipStream_t s) {
-    switch (K) {
-        case 8: return launch_search_far_k<DP, 8>(a, grid, s);
-        case 16: return launch_search_far_k<DP, 16>(a, grid, s);
-        case 32: return launch_search_far_k<DP, 32>(a, grid, s);
-        case 64: return launch_search_far_k<DP, 64>(a, grid, s);
-        default: return hipErrorInvalidValue;
+hipError_t launch_search_far(const SearchArgs &a, int kk, int grid, hipStream_t s) {
+    if (kk <= 8) return launch_search_far_k<DP, 8>(a, grid, s);
+    if constexpr (DP <= 8) {
+        if (kk <= 10) return launch_search_far_k<DP, 10>(a, grid, s);
+        if (kk <= 12) return launch_search_far_k<DP, 12>(a, grid, s);
     }
+    if (kk <= 16) return launch_search_far_k<DP, 16>(a, grid, s);
+    if constexpr (DP <= 8) {
+        if (kk <= 20) return launch_search_far_k<DP, 20>(a, grid, s);
+    }
+    if (kk <= 32) return launch_search_far_k<DP, 32>(a, grid, s);
+    if (kk <= 64) return launch_search_far_k<DP, 64>(a, grid, s);
+    return hipErrorInvalidValue;
 }
 
 }  // namespace knnx
