@@ -214,7 +214,7 @@ knn_status search(const knn_tree *ref, const knn_tree *query, int k, const knn_o
     const bool whole = dbg || opts.stats || opts.seed_radius || opts.leaf_kth_out || wlog_path;
     const bool few = !pair && ref->dp <= 16 && (!bf16 || mt) && !whole &&
                      opts.bound != KNN_BOUND_NONE && k + (opts.exclude_self ? 1 : 0) <= kFewList &&
-                     qt->n <= kFewQueries;
+                     few_queries(qt->n, ref->n, ref->d);
     // few slots: several waves share one.  The pair sweep: the four waves of a
     // workgroup take one pair of leaves while that leaves CUs idle otherwise
     const int split = pair ? (pair_parts(nq_leaves) ? 1 : 0)

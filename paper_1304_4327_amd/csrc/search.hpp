@@ -127,10 +127,17 @@ hipError_t launch_search_mt_d32(const SearchArgs &a, int K, int grid, hipStream_
 
 // one query per wave (search_few.hip): strides up to 16, every pruning bound
 // but KNN_BOUND_NONE, no seed, no counters; lists of kk <= kFewList entries.
-// Up to kFewQueries queries it beats the slot-per-wave walk: that one lasts as
-// long as its slowest wave until the chip is full.
+// The slot-per-wave walk lasts as long as its slowest wave until the chip is
+// full, and a slot's queries open the more of the reference tree the sparser
+// they lie in it; one query per wave costs the same per query throughout.
+// Measured (us, walk against one query per wave; k = 10, mixtures, d = 3):
+//   64,000 queries: 225 / 116 of 10,000 points, 798 / 132 of 200,000
+//   256,000 queries: 266 / 370 of 10,000, 565 / 419 of 200,000, 959 / 443 of 1.5M
+// and d = 8: 64,000 of 10,000 555 / 201, 256,000 of 200,000 3453 / 1987.
 constexpr int kFewList = 62;
-constexpr int64_t kFewQueries = 32768;
+inline bool few_queries(int64_t n_q, int64_t n_ref, int d) {
+    return n_q <= 65536 + n_ref / (d <= 4 ? 6 : 2);
+}
 hipError_t launch_search_few_d(const SearchArgs &a, int d, int64_t n_q, hipStream_t s);
 
 // the d = 64 sweep with two query leaves per wave (search_pair_d64.hip): the
