@@ -193,6 +193,13 @@ knn_status search(const knn_tree *ref, const knn_tree *query, int k, const knn_o
     // matrix-core tiles (two query leaves per wave, its own seeded pass)
     const bool mt = bf16 && !dbg && (ref->dp == 16 || ref->dp == 32) && K <= 16;
     if (mt) lpl_log2 = 5;
+    // FP32 at strides 8 and 16: the same kernel where the plain form would take
+    // two leaves a wave too (the visit order depends on the slot); it returns
+    // what that form returns: 2M queries of 2M points at d = 8, k = 10 67 ms
+    // plain, 54 here; 150,000 points on themselves at d = 13, k = 7 1.72 ms
+    // plain, 1.31 here.  The seeded form stays plain.
+    const bool mt32 = !bf16 && !dbg && !opts.seed_radius && (ref->dp == 8 || ref->dp == 16) &&
+                      lpl_log2 == 5 && ref->leaf_slots <= 32 && K <= 16;
     const int NG = 64 >> lpl_log2;
     const int nq_leaves = int(qt->n_leaves);
     if (dbg && (ref->d != 3 || bf16 || opts.seed_radius || K > 16))
@@ -270,6 +277,7 @@ knn_status search(const knn_tree *ref, const knn_tree *query, int k, const knn_o
     a.k = k;
     a.lpl_log2 = lpl_log2;
     a.split = split;
+    a.walk_ties = bf16 ? 0 : 1;
     a.bound = opts.bound;
     a.self = opts.exclude_self ? 1 : 0;
     a.seed = opts.seed_radius;
@@ -314,7 +322,6 @@ knn_status search(const knn_tree *ref, const knn_tree *query, int k, const knn_o
         KNN_HIP(zero_words(dstats, 2 * 2 * ST_COUNT, s));
     }
     if (pair) {  // the reference-side operands, made once per search
-        a.walk_ties = bf16 ? 0 : 1;
         const int nl = int(ref->first_leaf) + 1;
         const size_t pl = size_t((nl + kSweepBlock - 1) / kSweepBlock) * kSweepBlock;  // padded leaves
         uint16_t *abf = nullptr, *cbf = nullptr;
@@ -354,7 +361,8 @@ knn_status search(const knn_tree *ref, const knn_tree *query, int k, const knn_o
     KNN_HIP(dbg    ? launch_search_valu_debug_d3(a, K, grid, s)
             : few  ? launch_search_few_d(a, ref->d, qt->n, s)
             : pair ? launch_search_pair_dp64(a, k + (opts.exclude_self ? 1 : 0), s)
-            : mt   ? (ref->dp == 16 ? launch_search_mt_d16(a, K, grid, s)
+            : mt32 && ref->dp == 8 ? launch_search_mt_d8(a, K, grid, s)
+            : mt || mt32 ? (ref->dp == 16 ? launch_search_mt_d16(a, K, grid, s)
                                     : launch_search_mt_d32(a, K, grid, s))
             : bf16 ? launch_mfma(a, ref->dp, K, grid, s)
                    : launch_valu(a, ref->d, K, grid, s));

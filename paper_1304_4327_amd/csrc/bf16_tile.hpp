@@ -15,7 +15,7 @@
 //
 // Error bound.  With u_b = 2^-8 (BF16 round to nearest) and u = 2^-24,
 //   |D + ||q'||^2 - ||q - r||^2| <= 2 (2 u_b + u_b^2) |q'| |r'|
-//                                   + (DP + 8) u (|q'| + |r'|)^2 :
+//                                   + (DP + 16) u (|q'| + |r'|)^2 :
 // products of BF16 values are exact in FP32, the rounding of both operands
 // gives the first term, the FP32 centring, norms and accumulation the
 // second.  The margin takes |r'| <= R, the largest row of the tile, and
@@ -36,7 +36,7 @@ template <int DP>
 struct Bf16Margin {
     static constexpr float ub = 0x1p-8f;
     static constexpr float C1 = 1.25f * 2.0f * (2.0f * ub + ub * ub);
-    static constexpr float C2 = 1.25f * (DP + 8) * 0x1p-24f;
+    static constexpr float C2 = 1.25f * (DP + 16) * 0x1p-24f;
 };
 
 // margin M(q, tile) for |q'| = qlen and the tile's largest |r'| <= rlen
@@ -44,6 +44,14 @@ template <int DP>
 __device__ __forceinline__ float bf16_margin(float qlen, float rlen) {
     return Bf16Margin<DP>::C1 * qlen * rlen +
            Bf16Margin<DP>::C2 * (qlen + rlen) * (qlen + rlen);
+}
+
+// The d = 8 form: the rows enter as the sum of two BF16 parts (2^-16), the
+// queries as one, so the error is at most 2 (u_b + 2^-16 (1 + u_b)) |q'| |r'|
+// plus the FP32 terms of 16 products, the norm's and the threshold's.
+__device__ __forceinline__ float bf16_margin_d8(float qlen, float rlen) {
+    constexpr float C1 = 1.25f * 2.0f * (0x1p-8f + 0x1p-15f), C2 = 1.25f * 40.0f * 0x1p-24f;
+    return C1 * qlen * rlen + C2 * (qlen + rlen) * (qlen + rlen);
 }
 
 // This lane's query operand: -2 (q - c) in BF16 over dimensions
@@ -154,6 +162,36 @@ __device__ __forceinline__ f32x16_t bf16_norm_init(float rn, bool vr, int h) {
     }
     const f32x16_t zero = {};
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(an, ones, zero, 0, 0, 0);
+}
+
+// The accumulators' initial values ||r_i'||^2 - thr_j: the product above with
+// three more terms, the threshold of column lane % 32 split the same way
+// against ones.  An unused column (use false) starts at +inf, as a row past
+// the tile does.  Both splits are exact, so the sums round as FP32 sums do:
+// the margins count these terms.
+__device__ __forceinline__ f32x16_t bf16_start(float rn, bool vr, float thr, bool use, int h) {
+    const __bf16 n0 = (__bf16)(vr ? rn : __builtin_inff());
+    const float r1 = vr ? rn - float(n0) : 0.f;
+    const __bf16 n1 = (__bf16)r1;
+    const __bf16 n2 = (__bf16)(r1 - float(n1));
+    const float mt = -thr;
+    const __bf16 t0 = (__bf16)(use ? mt : __builtin_inff());
+    const float s1 = use ? mt - float(t0) : 0.f;
+    const __bf16 t1 = (__bf16)s1;
+    const __bf16 t2 = (__bf16)(s1 - float(t1));
+    bf16x8_t a = {}, b = {};
+    if (h == 0) {
+        a[0] = n0;
+        a[1] = n1;
+        a[2] = n2;
+        a[3] = a[4] = a[5] = (__bf16)1.0f;
+        b[0] = b[1] = b[2] = (__bf16)1.0f;
+        b[3] = t0;
+        b[4] = t1;
+        b[5] = t2;
+    }
+    const f32x16_t zero = {};
+    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, zero, 0, 0, 0);
 }
 
 // Largest |r'| of a tile from each lane's full row norm rn (rows past the

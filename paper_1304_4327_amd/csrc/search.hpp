@@ -43,7 +43,7 @@ struct SearchArgs {
     int d, k, lpl_log2;
     int bound;          // knn_bound
     int self;           // exclude reference position == query position
-    int walk_ties;      // k_search_pair: equal k-th distances in the walk's order
+    int walk_ties;      // FP32 requests: among equal distances the plain walk's order
     const float *seed;  // per query leaf, or NULL
     int64_t *out_idx;
     float *out_dist;
@@ -122,6 +122,8 @@ hipError_t launch_search_valu_debug_d3(const SearchArgs &a, int K, int grid, hip
 // (search_mt_d*.hip): 16 or 32 computed dimensions, two query leaves per wave
 // (lpl_log2 = 5), reference leaves of <= 32 points, K <= 16; the seeded form
 // when a.seed is set
+// (stride 8 in the plain form only)
+hipError_t launch_search_mt_d8(const SearchArgs &a, int K, int grid, hipStream_t s);
 hipError_t launch_search_mt_d16(const SearchArgs &a, int K, int grid, hipStream_t s);
 hipError_t launch_search_mt_d32(const SearchArgs &a, int K, int grid, hipStream_t s);
 

@@ -228,7 +228,8 @@ __global__ __launch_bounds__(256) void k_search_few(const SearchArgs a) {
         // equal distances at the k-th place: the ones the walk meets first
         const uint64_t grp = ballot(x == xk);
         const int g0 = __builtin_ctzll(grp), g1 = 63 - __builtin_clzll(grp);
-        const int ql = leaf_node_of(qpos, n_q, a.q_first_leaf) - a.q_first_leaf;
+        int q0;
+        const int ql = leaf_node_of(qpos, n_q, a.q_first_leaf, q0) - a.q_first_leaf;
         for (int e = g1; e > g0; --e) {
             bool swapped = false;
             for (int t = g0; t < e; ++t) {

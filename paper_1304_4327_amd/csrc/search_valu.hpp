@@ -49,16 +49,21 @@
 //     pass.
 // The plain form carries none of the other two forms' state.
 //
-// Matrix-core tiles (MT, d = 16 or 32, two leaves of 17..32 points per wave,
-// lists of up to 16): the same walk, Score and bounds; a reference leaf's
-// BaseCase distances come from the BF16 tile of bf16_tile.hpp, centred on
-// the union box centre c of the wave's two leaves, one product per query leaf
-// (the 32 queries of leaf g are its columns).  Lane l is then both query
-// l % 32 of leaf l / 32 and column l % 32 of half l / 32 of the products, so
-// it holds half of its own query's 32 values and takes the other half from
-// lane l ^ 32.  A row is a candidate when its value minus the proven margin
-// beats min(D_p[k], B); candidates are re-scored in FP64 before they may
-// enter the list, so the lists are those of the FP32 form.
+// Matrix-core tiles (MT, d = 8, 16 or 32, two leaves of 17..32 points per
+// wave, lists of up to 16): the same walk, Score and bounds; which rows of a
+// reference leaf can enter a list is read off the BF16 tile of bf16_tile.hpp,
+// centred on the union box centre c of the wave's two leaves, one product per
+// query leaf (the 32 queries of leaf g are its columns), and only those rows
+// get a distance, computed as in the plain form (FP32 differences at d = 8,
+// FP64 above).  Lane l is then both query l % 32 of leaf l / 32 and column
+// l % 32 of half l / 32 of the products, so it holds the bits of half of its
+// own query's 32 rows and takes the other half's from lane l ^ 32.  A row is a
+// candidate when its value minus the proven margin beats min(D_p[k], B); so
+// the lists are those of the plain form, for either precision request.
+//
+// What bounds it: instruction issue.  The plain form spends about 2 d + 2
+// instructions on every reference point of a tile (600 a tile at d = 8), the
+// tile here about 120 in all.
 
 #pragma once
 
@@ -120,8 +125,8 @@ template <int D, int K, int LG, int MODE, bool MT>
 __device__ __forceinline__ void search_valu_body(const SearchArgs &a) {
     constexpr bool DBG = MODE == kValuDebug;
     constexpr bool SEEDED = MODE == kValuSeeded;
-    static_assert(!MT || ((D == 16 || D == 32) && LG == 5 && !DBG),
-                  "matrix-core tiles: d = 16 or 32, two leaves of <= 32 points per wave");
+    static_assert(!MT || ((D == 8 || D == 16 || D == 32) && LG == 5 && !DBG),
+                  "matrix-core tiles: d = 8, 16 or 32, two leaves of <= 32 points per wave");
     constexpr int DP = stride_for(D);
     constexpr bool RESCORE = D > 8;
     // several waves may share a slot (split_for); up to stride 16 few queries
@@ -189,8 +194,10 @@ __device__ __forceinline__ void search_valu_body(const SearchArgs &a) {
                 lo = xor_level(lo, l, OpMin());
                 hi = xor_level(hi, l, OpMax());
             }
-            ulo[j] = lo;
-            uhi[j] = hi;
+            // (the same in every lane; in scalar registers where the vector ones
+            // are short)
+            ulo[j] = MT ? uniform_f(lo) : lo;
+            uhi[j] = MT ? uniform_f(hi) : hi;
         }
     } else {
         float lo = lane < DP ? kInf : 0.f, hi = lane < DP ? -kInf : 0.f;
@@ -208,34 +215,55 @@ __device__ __forceinline__ void search_valu_body(const SearchArgs &a) {
     // MT: the centre c (union box centre), this lane's centre values at its
     // operand dimensions, |q - c| of its own query and the query operands
     // -2 (q - c) of both leaves (column l % 32 of leaf g is the query of lane
-    // 32 g + l % 32)
-    constexpr int S = MT ? DP / 16 : 1;
+    // 32 g + l % 32).  At d = 8 a k-step holds the dimensions twice, against
+    // the high and the low BF16 part of the reference rows.
+    constexpr int S = MT && DP > 16 ? DP / 16 : 1;
     const int hh = lane >> 5, jj = lane & 31;
     [[maybe_unused]] float tcen[S * 8];
     [[maybe_unused]] bf16x8_t bq0[S], bq1[S];
     [[maybe_unused]] float qn_mt = 0.f, qlen_mt = 0.f;
+    [[maybe_unused]] float qlen0 = 0.f, qlen1 = 0.f, base0 = 0.f, base1 = 0.f;
+    // this lane's value and its partner's, as (leaf 0's query jj, leaf 1's)
+    auto both = [&](float v, float &v0, float &v1) {
+        const float o = __shfl_xor(v, 32);
+        v0 = hh ? o : v;
+        v1 = hh ? v : o;
+    };
     if constexpr (MT) {
-        const float cl = lane < DP ? 0.5f * (ulo[0] + uhi[0]) : 0.f;
-#pragma unroll
-        for (int d0 = 0; d0 < D; ++d0) {
-            const float df = q[d0] - __shfl(cl, d0);
-            qn_mt = fmaf(df, df, qn_mt);
-        }
-        qlen_mt = sqrtf(qn_mt);
-#pragma unroll
-        for (int s = 0; s < S; ++s) {
+        if constexpr (D == 8) {
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
-                const int da = s * 16 + e, db = da + 8;
-                const float ca = __shfl(cl, da), cb = __shfl(cl, db);
-                const float c = hh ? cb : ca;
-                tcen[s * 8 + e] = c;
-                const float a0 = __shfl(q[da], jj), b0 = __shfl(q[db], jj);
-                const float a1 = __shfl(q[da], 32 + jj), b1 = __shfl(q[db], 32 + jj);
-                bq0[s][e] = (__bf16)(-2.0f * ((hh ? b0 : a0) - c));
-                bq1[s][e] = (__bf16)(-2.0f * ((hh ? b1 : a1) - c));
+                const float c = uniform_f(0.5f * (ulo[e] + uhi[e]));
+                tcen[e] = c;
+                const float df = q[e] - c;
+                qn_mt = fmaf(df, df, qn_mt);
+                bq0[0][e] = (__bf16)(-2.0f * (__shfl(q[e], jj) - c));
+                bq1[0][e] = (__bf16)(-2.0f * (__shfl(q[e], 32 + jj) - c));
+            }
+        } else {
+            const float cl = lane < DP ? 0.5f * (ulo[0] + uhi[0]) : 0.f;
+#pragma unroll
+            for (int d0 = 0; d0 < D; ++d0) {
+                const float df = q[d0] - __shfl(cl, d0);
+                qn_mt = fmaf(df, df, qn_mt);
+            }
+#pragma unroll
+            for (int s = 0; s < S; ++s) {
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    const int da = s * 16 + e, db = da + 8;
+                    const float ca = __shfl(cl, da), cb = __shfl(cl, db);
+                    const float c = hh ? cb : ca;
+                    tcen[s * 8 + e] = c;
+                    const float a0 = __shfl(q[da], jj), b0 = __shfl(q[db], jj);
+                    const float a1 = __shfl(q[da], 32 + jj), b1 = __shfl(q[db], 32 + jj);
+                    bq0[s][e] = (__bf16)(-2.0f * ((hh ? b0 : a0) - c));
+                    bq1[s][e] = (__bf16)(-2.0f * ((hh ? b1 : a1) - c));
+                }
             }
         }
+        qlen_mt = sqrtf(qn_mt);
+        both(qlen_mt, qlen0, qlen1);
     }
     const float lam2 = has_leaf ? 2.0f * a.qlam[qnode] : 0.f;
     // seeded form: a seed is only a pruning radius; NaN or negative values
@@ -268,29 +296,36 @@ __device__ __forceinline__ void search_valu_body(const SearchArgs &a) {
     };
 
     // Score a reference node from its box: keep when any point's d_min^2 to
-    // the box is within its bound; the visit-order key is the wave-uniform
-    // d_min^2 between the union of the wave's leaf boxes and the node's box
-    auto score_box = [&](const float *b, float &key_out) -> bool {
-        float sd = 0.f, u = 0.f;
+    // the box is within its bound
+    auto score_box = [&](const float *b) -> bool {
+        float sd = 0.f;
 #pragma unroll
         for (int j = 0; j < D; ++j) {
-            const float lo = b[j], hi = b[DP + j];
-            const float gap = fmaxf(fmaxf(lo - q[j], q[j] - hi), 0.0f);
+            const float gap = fmaxf(fmaxf(b[j] - q[j], q[j] - b[DP + j]), 0.0f);
             sd = fmaf(gap, gap, sd);
-            if constexpr (!WIDE) {
-                const float ug = fmaxf(fmaxf(lo - uhi[j], ulo[j] - hi), 0.0f);
+        }
+        const bool keep = valid && !(sd > point_bound2() * kSlack);
+        return ballot(keep) != 0;
+    };
+    // visit-order key, taken only where both children are kept: the
+    // wave-uniform d_min^2 between the union of the wave's leaf boxes and the
+    // node's box
+    // (high d: lo, hi are dimension `lane` of the node's box, loaded with the
+    // scores' boxes so that the key waits for nothing)
+    auto box_key = [&](const float *b, float lo, float hi) -> float {
+        float u = 0.f;
+        if constexpr (!WIDE) {
+#pragma unroll
+            for (int j = 0; j < D; ++j) {
+                const float ug = fmaxf(fmaxf(b[j] - uhi[j], ulo[j] - b[DP + j]), 0.0f);
                 u = fmaf(ug, ug, u);
             }
-        }
-        if constexpr (WIDE) {
-            const float lo = lane < DP ? b[lane] : 0.f, hi = lane < DP ? b[DP + lane] : 0.f;
+        } else {
             const float ug = fmaxf(fmaxf(lo - uhi[0], ulo[0] - hi), 0.0f);
             u = ug * ug;
             u = sum_dim_lanes<DP>(u);
         }
-        const bool keep = valid && !(sd > point_bound2() * kSlack);
-        key_out = uniform_f(u);
-        return ballot(keep) != 0;
+        return uniform_f(u);
     };
     // debug form: one record per Score call with each leaf's bound
     auto log_score = [&](int node, bool keep) {
@@ -315,9 +350,9 @@ __device__ __forceinline__ void search_valu_body(const SearchArgs &a) {
             }
         }
     };
-    auto score = [&](int node, float &key_out) -> bool {
+    auto score = [&](int node) -> bool {
         ++n_score;
-        const bool keep = score_box(a.rbox + int64_t(node) * 2 * DP, key_out);
+        const bool keep = score_box(a.rbox + int64_t(node) * 2 * DP);
         log_score(node, keep);
         return keep;
     };
@@ -329,6 +364,13 @@ __device__ __forceinline__ void search_valu_body(const SearchArgs &a) {
         // grandchildren's boxes (contiguous), or the first lines of both
         // leaves' tiles
         uint32_t p0 = 0, p1 = 0, p2 = 0;
+        if constexpr (DP == 8) {
+            // (four boxes of 64 bytes)
+            const float *g = a.rbox + int64_t(c0 < a.r_first_leaf ? 2 * c0 + 1 : c0) * 2 * DP;
+            p0 = __float_as_uint(g[0]);
+            p1 = __float_as_uint(g[16]);
+            p2 = c0 < a.r_first_leaf ? __float_as_uint(g[32]) ^ __float_as_uint(g[48]) : 0u;
+        }
         if constexpr (DP <= 4) {
             const bool inner = c0 < a.r_first_leaf;
             const float *g = inner ? a.rbox + int64_t(2 * c0 + 1) * 2 * DP
@@ -339,8 +381,17 @@ __device__ __forceinline__ void search_valu_body(const SearchArgs &a) {
             p1 = __float_as_uint(g[s1]);
             p2 = __float_as_uint(g[s2]);
         }
-        k0 = score_box(b, m0);
-        k1 = score_box(b + 2 * DP, m1);
+        float w[4] = {0.f, 0.f, 0.f, 0.f};
+        if constexpr (WIDE) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) w[i] = lane < DP ? b[i * DP + lane] : 0.f;
+        }
+        k0 = score_box(b);
+        k1 = score_box(b + 2 * DP);
+        if (k0 && k1) {
+            m0 = box_key(b, w[0], w[1]);
+            m1 = box_key(b + 2 * DP, w[2], w[3]);
+        }
         log_score(c0, k0);
         log_score(c0 + 1, k1);
         tacc ^= q0 ^ q1 ^ q2;
@@ -398,6 +449,18 @@ __device__ __forceinline__ void search_valu_body(const SearchArgs &a) {
         }
         bound2 = SEEDED ? fminf(b, seed2) : b;
     };
+    // MT: what column jj's values of the two products are compared with, but
+    // for the margin: min(D_p[k], B)^2 (1 + 2^-16) - |q - c|^2
+    auto refresh_base = [&]() {
+        if constexpr (MT) both(fminf(dist[K - 1], bound2) * kSlack - qn_mt, base0, base1);
+    };
+    [[maybe_unused]] bool valid_0 = false, valid_1 = false;  // columns in use
+    if constexpr (MT) {
+        refresh_base();
+        const uint64_t vm = ballot(valid);
+        valid_0 = (vm >> jj) & 1;
+        valid_1 = (vm >> (32 + jj)) & 1;
+    }
 
     // BaseCase over one reference leaf: every lane against each reference
     // point, CH points per batch.  A candidate must beat min(D_p[k], B):
@@ -413,8 +476,10 @@ __device__ __forceinline__ void search_valu_body(const SearchArgs &a) {
         n_pairs += uint64_t(cnt) * uint64_t(n_valid);
         if constexpr (MT) {
             // reference operand: row jj, the dimensions of half hh, centred
+            // (d = 8: all dimensions, the high BF16 part in half 0, the low
+            // one in half 1)
             const bool vr = jj < cnt;
-            const float *row = rp + (vr ? jj : 0) * DP + hh * 8;
+            const float *row = rp + (vr ? jj : 0) * DP + (D == 8 ? 0 : hh * 8);
             bf16x8_t ar[S];
             float rn = 0.f;
 #pragma unroll
@@ -424,45 +489,64 @@ __device__ __forceinline__ void search_valu_body(const SearchArgs &a) {
                 const float xv[8] = {x0.x, x0.y, x0.z, x0.w, x1.x, x1.y, x1.z, x1.w};
 #pragma unroll
                 for (int e = 0; e < 8; ++e) {
-                    const float rd = vr ? xv[e] - tcen[s * 8 + e] : 0.f;
+                    // (a row past the leaf repeats row 0: its start value is
+                    // +inf, and a select here made the compiler load the row
+                    // in two dependent steps)
+                    const float rd = xv[e] - tcen[s * 8 + e];
                     rn = fmaf(rd, rd, rn);
-                    ar[s][e] = (__bf16)rd;
+                    if constexpr (D == 8) {
+                        const __bf16 h = (__bf16)rd;
+                        const __bf16 l = (__bf16)(rd - float(h));
+                        ar[0][e] = hh ? l : h;
+                    } else {
+                        ar[s][e] = (__bf16)rd;
+                    }
                 }
             }
-            rn += __shfl_xor(rn, 32);  // the row's whole norm
-            // largest |r - c| of the tile (hardware square root, nudged up:
-            // the margin only needs an upper bound)
-            const float rlen =
-                __builtin_amdgcn_sqrtf(uniform_f(reduce32(vr ? rn : 0.f, OpMax()))) * (1.0f + 0x1p-20f);
-            // the accumulators start at the row norms, from one more product
-            // (the norms never leave their lanes: no LDS, no fence)
-            const f32x16_t accn = bf16_norm_init(rn, vr, hh);
-            f32x16_t acc0 = accn, acc1 = accn;
+            if constexpr (D != 8) rn += __shfl_xor(rn, 32);  // the row's whole norm
+            // largest |r - c| of the tile
+            const float rlen = bf16_tile_rlen(rn, vr);
+            // thresholds of the two columns: base + margin (the margin is 1.25
+            // times the proven bound, so the strict test keeps every row the
+            // bound admits), capped at the largest BF16 number
+            auto margin = [&](float ql) {
+                return D == 8 ? bf16_margin_d8(ql, rlen) : bf16_margin<DP>(ql, rlen);
+            };
+            const float thr0 = fminf(base0 + margin(qlen0), 0x1.fep127f);
+            const float thr1 = fminf(base1 + margin(qlen1), 0x1.fep127f);
+            // the accumulators start at |r - c|^2 - threshold, from one more
+            // product each: a value's sign says whether the row is a candidate
+            f32x16_t acc0 = bf16_start(rn, vr, thr0, valid_0, hh);
+            f32x16_t acc1 = bf16_start(rn, vr, thr1, valid_1, hh);
 #pragma unroll
             for (int s = 0; s < S; ++s) {
                 acc0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ar[s], bq0[s], acc0, 0, 0, 0);
                 acc1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ar[s], bq1[s], acc1, 0, 0, 0);
             }
-            // this lane's query: rows of half hh from its own leaf's product,
-            // rows of the other half from lane ^ 32; keep D < T - |q'|^2 + M
-            // (the margin is 1.25 times the proven bound, so the strict test
-            // keeps every row the bound admits).  T is capped at FLT_MAX:
-            // rows past the tile hold +inf and never pass, valid rows always
-            // do while a list is not full.  Bit r: the sign of D - thr.
-            const float marg = bf16_margin<DP>(qlen_mt, rlen);
-            const float thr =
-                valid ? fminf(fminf(dist[K - 1], bound2) * kSlack - qn_mt + marg, 0x1.fffffep127f) : -kInf;
-            uint32_t mask = 0;
+            // most tiles hold no candidate: one OR of all signs
+            uint32_t any = 0;
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const float own = hh ? acc1[r] : acc0[r];
-                const float oth = __shfl_xor(hh ? acc0[r] : acc1[r], 32);
-                mask |= (__float_as_uint(own - thr) >> 31) << r;
-                mask |= (__float_as_uint(oth - thr) >> 31) << (16 + r);
+            for (int r = 0; r < 16; ++r) any |= __float_as_uint(acc0[r]) | __float_as_uint(acc1[r]);
+            if (!ballot(int32_t(any) < 0)) return;  // lists unchanged, and so the bound
+            // bit r: the sign of value r; this lane keeps the rows of half hh
+            // for its own query and takes the other half's from lane ^ 32
+            uint32_t mk0 = 0, mk1 = 0;
+#pragma unroll
+            for (int r = 15; r >= 0; --r) {
+                mk0 = __builtin_amdgcn_alignbit(mk0, __float_as_uint(acc0[r]), 31);
+                mk1 = __builtin_amdgcn_alignbit(mk1, __float_as_uint(acc1[r]), 31);
             }
-            if (!ballot(mask != 0)) return;  // lists unchanged, and so the bound
+            const uint32_t own = hh ? mk1 : mk0;
+            const uint32_t oth = uint32_t(__shfl_xor(int(hh ? mk0 : mk1), 32));
+            // FP32 requests take the rows in ascending order, as the plain
+            // form does (it decides which of two equal distances is kept);
+            // BF16 ones first the rows of their half
+            auto spread = [](uint32_t m, int h) {
+                return ((m & 0xfu) | ((m & 0xf0u) << 4) | ((m & 0xf00u) << 8) | ((m & 0xf000u) << 12)) << (4 * h);
+            };
+            uint32_t mask = a.walk_ties ? spread(own, hh) | spread(oth, 1 - hh) : own | (oth << 16);
             n_cand += __popc(mask);
-            // survivors: one per lane per round, FP64 re-score, insert (a lane
+            // survivors: one per lane per round, re-scored, inserted (a lane
             // without one re-scores row 0 and inserts +inf, a no-op)
 #pragma unroll 1
             for (int pass = 0; pass < 32; ++pass) {
@@ -472,13 +556,25 @@ __device__ __forceinline__ void search_valu_body(const SearchArgs &a) {
                 const int b = has ? __builtin_ctz(mask) : 0;
                 mask &= mask - 1u;
                 const int rb = b & 15, hb = b < 16 ? hh : 1 - hh;
-                const int rw = 8 * (rb >> 2) + 4 * hb + (rb & 3);
-                const float x = (float)d2_fp64<D, true>(q, rp + rw * DP);
+                const int rw = a.walk_ties ? b : 8 * (rb >> 2) + 4 * hb + (rb & 3);
+                const float *rq = rp + rw * DP;
+                float x;
+                if constexpr (RESCORE) {
+                    x = (float)d2_fp64<D, true>(q, rq);
+                } else {
+                    x = 0.f;
+#pragma unroll
+                    for (int j = 0; j < D; ++j) {
+                        const float df = q[j] - rq[j];
+                        x = fmaf(df, df, x);
+                    }
+                }
                 const bool ins = has && x < dist[K - 1];
                 n_ins += ins ? 1u : 0u;
                 insert(ins ? x : kInf, base + rw);
             }
             refresh_bound();
+            refresh_base();
             return;
         }
         const float bnd = bound2 * kSlack;
@@ -559,10 +655,10 @@ __device__ __forceinline__ void search_valu_body(const SearchArgs &a) {
     // twice, the walk made the kernel much slower)
     for (int pass = 0;; ++pass) {
         if (!replay) {
-            float dm0, dm1;
+            float dm0 = 0.f, dm1 = 0.f;
             int node = 0, depth = 0;
             uint64_t nearbits = 0;
-            bool down = score(0, dm0);
+            bool down = score(0);
             if (down) {
                 // outer loop: one reference leaf per iteration; the inner walk
                 // leaves the k-lists untouched, so they are not carried through
@@ -601,7 +697,7 @@ __device__ __forceinline__ void search_valu_body(const SearchArgs &a) {
                             const bool near_right = (nearbits >> depth) & 1;
                             if (is_right == near_right) {
                                 const int far = is_right ? node - 1 : node + 1;
-                                if (score(far, dm0)) {
+                                if (score(far)) {
                                     node = far;
                                     ++depth;
                                     down = true;
@@ -658,6 +754,12 @@ __device__ __forceinline__ void search_valu_body(const SearchArgs &a) {
             // until they fill
             seed2 = (a.bound == KNN_BOUND_NONE || !fb_leaf) ? kInf : pb * pb;
             bound2 = seed2;
+            if constexpr (MT) {
+                refresh_base();
+                const uint64_t vm = ballot(valid);
+                valid_0 = (vm >> jj) & 1;
+                valid_1 = (vm >> (32 + jj)) & 1;
+            }
         }
     }
     valid = valid0;
@@ -758,11 +860,12 @@ k_search_valu(const SearchArgs a) {
     search_valu_body<D, K, LG, MODE, false>(a);
 }
 
-// matrix-core tiles; at d = 16 the register budget of three waves per SIMD
-// keeps the accumulators in ordinary registers (four waves fit), at d = 32
-// it would spill
+// matrix-core tiles; at d <= 16 four waves per SIMD fit without spills in the
+// plain form with short lists, three otherwise (the target also keeps the
+// accumulators in ordinary registers); at d = 32 it would spill
 template <int D, int K, int MODE = kValuPlain>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 16 ? 3 : 1))) void
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(
+    D > 16 ? 1 : MODE == kValuPlain && K <= 11 ? 4 : 3))) void
 k_search_valu_mt(const SearchArgs a) {
     search_valu_body<D, K, 5, MODE, true>(a);
 }

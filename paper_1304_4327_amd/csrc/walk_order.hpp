@@ -10,10 +10,11 @@
 
 namespace knnx {
 
-// the leaf node that holds tree position pos of a tree over n points (a
+// the leaf node (and its first position) that holds tree position pos of a tree over n points (a
 // node's left child takes floor(c / 2) of its c points)
-__device__ inline int leaf_node_of(int pos, int n, int first_leaf) {
-    int node = 0, start = 0, cnt = n;
+__device__ inline int leaf_node_of(int pos, int n, int first_leaf, int &start) {
+    int node = 0, cnt = n;
+    start = 0;
     while (node < first_leaf) {
         const int half = cnt >> 1;
         if (pos < start + half) {
@@ -31,7 +32,9 @@ __device__ inline int leaf_node_of(int pos, int n, int first_leaf) {
 // Whether the walk of the slot of query leaf qleaf (1 << ng_log2 sibling
 // leaves) meets tree position pb before pa: of the two children of their
 // lowest common ancestor, the one nearer to the slot's union box is entered
-// first (the left one on equal keys); within a leaf the smaller position.
+// first (the left one on equal keys); within a leaf the smaller position, for
+// a BF16 request (a.walk_ties 0) the rows of the query's half of the tile
+// first.
 // The keys are computed as the walk computes them.  Wave-uniform arguments,
 // every lane active.
 template <int D>
@@ -41,8 +44,13 @@ __device__ inline bool walk_meets_second_first(const SearchArgs &a, int pa, int 
     constexpr float kInf = __builtin_inff();
     const int lane = threadIdx.x & 63;
     const int n = a.rrange[0].y;
-    int na = leaf_node_of(pa, n, a.r_first_leaf), nb = leaf_node_of(pb, n, a.r_first_leaf);
-    if (na == nb) return pb < pa;
+    int sa, sb;
+    int na = leaf_node_of(pa, n, a.r_first_leaf, sa), nb = leaf_node_of(pb, n, a.r_first_leaf, sb);
+    if (na == nb) {
+        const int ha = ((pa - sa) >> 2) & 1, hb = ((pb - sb) >> 2) & 1;
+        if (!a.walk_ties && ha != hb) return hb == (qleaf & 1);
+        return pb < pa;
+    }
     while (((na - 1) >> 1) != ((nb - 1) >> 1)) {
         na = (na - 1) >> 1;
         nb = (nb - 1) >> 1;

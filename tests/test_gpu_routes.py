@@ -1,8 +1,10 @@
-"""The kernels that serve a call beside the slot-per-wave walk return what the
-walk returns, ties at the k-th place included: one query per wave (few
-queries, d <= 16) against the walk that a call with counters takes, and the
-FP32 sweep at d > 32 against the no-alloc entry's walk.  Bit for bit: the
-distances are the same numbers and every tie follows the walk's order."""
+"""The kernels that serve a call beside the plain slot-per-wave walk return what
+it returns, ties at the k-th place included: one query per wave (few queries,
+d <= 16) against the walk that a call with counters takes (plain, or with
+matrix-core tiles at 5 <= d <= 16 with leaves of 17 to 32 points and lists of
+up to 16), and the FP32 sweep at d > 32 against the no-alloc entry's walk.  Bit
+for bit: the distances are the same numbers and every tie follows the walk's
+order."""
 import numpy as np
 import pytest
 
@@ -33,7 +35,8 @@ def _trees(ref, q, leaf):
 # reference sizes: one leaf; one, two and three steps of six levels; k from 1
 # to the longest list of the kernel (62 with the query's own point)
 @pytest.mark.parametrize("n_ref,leaf,k", [(30, 32, 7), (700, 32, 1), (3000, 20, 62), (3000, 64, 10),
-                                          (9000, 2, 5), (60_000, 16, 16)])
+                                          (9000, 2, 5), (60_000, 16, 16), (20_000, 32, 10),
+                                          (5000, 24, 14)])
 @pytest.mark.parametrize("d,kind", [(1, "random"), (2, "lattice"), (3, "twice"), (4, "random"),
                                     (5, "random"), (8, "twice"), (13, "random"), (16, "twice")])
 def test_one_query_per_wave_equals_the_walk(n_ref, leaf, k, d, kind):
