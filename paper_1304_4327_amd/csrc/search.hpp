@@ -136,9 +136,11 @@ hipError_t launch_search_mt_d32(const SearchArgs &a, int K, int grid, hipStream_
 //   64,000 queries: 225 / 116 of 10,000 points, 798 / 132 of 200,000
 //   256,000 queries: 266 / 370 of 10,000, 565 / 419 of 200,000, 959 / 443 of 1.5M
 // and d = 8: 64,000 of 10,000 555 / 201, 256,000 of 200,000 3453 / 1987.
+// Above d = 8 its tiles re-score in FP64 and the walk has matrix-core tiles:
+// 1M of 4M at d = 16 takes 10.8 ms there, 13.1 ms here.
 constexpr int kFewList = 62;
 inline bool few_queries(int64_t n_q, int64_t n_ref, int d) {
-    return n_q <= 65536 + n_ref / (d <= 4 ? 6 : 2);
+    return n_q <= 65536 + n_ref / (d <= 4 ? 6 : d <= 8 ? 2 : 8);
 }
 hipError_t launch_search_few_d(const SearchArgs &a, int d, int64_t n_q, hipStream_t s);
 
