@@ -1,5 +1,5 @@
 // C-ABI entry of the kernel density sums (include/knn.h): validation,
-// dispatch of k_kde by stride and leaf width, counters and timing.
+// dispatch of k_kde by dimension and leaf width, counters and timing.
 #include "search_kde.hpp"
 
 #include <cmath>
@@ -8,17 +8,25 @@
 namespace knnx {
 namespace {
 
-template <int DP>
+template <int D>
 hipError_t launch_kde(const KdeArgs &a, int lg, int grid, hipStream_t s) {
     if (lg == 5)
-        k_kde<DP, 5><<<grid, 256, 0, s>>>(a);
+        k_kde<D, 5><<<grid, 256, 0, s>>>(a);
     else
-        k_kde<DP, 6><<<grid, 256, 0, s>>>(a);
+        k_kde<D, 6><<<grid, 256, 0, s>>>(a);
     return hipGetLastError();
 }
 
-hipError_t launch_dp(const KdeArgs &a, int dp, int lg, int grid, hipStream_t s) {
-    switch (dp) {
+// computed dimensions: 2 and 3 as such, else the stride.  At d = 3 a seventh
+// of the time went to the padding dimension (1M points: 12.6 ms with it,
+// 11.0 without); the walks of the range, k-furthest and Boruvka kernels gain
+// nothing from it.
+int computed_dims(int d) { return d <= 2 ? 2 : d == 3 ? 3 : pad_dim(d); }
+
+hipError_t launch_dims(const KdeArgs &a, int dims, int lg, int grid, hipStream_t s) {
+    switch (dims) {
+        case 2: return launch_kde<2>(a, lg, grid, s);
+        case 3: return launch_kde<3>(a, lg, grid, s);
         case 4: return launch_kde<4>(a, lg, grid, s);
         case 8: return launch_kde<8>(a, lg, grid, s);
         case 16: return launch_kde<16>(a, lg, grid, s);
@@ -94,7 +102,7 @@ extern "C" knn_status knn_kde(const knn_tree *ref, const knn_tree *query, double
         KNN_HIP(hipEventRecord(ev[0], s));
     }
     a.stats = dstats;
-    KNN_HIP(launch_dp(a, ref->dp, lg, grid, s));
+    KNN_HIP(launch_dims(a, computed_dims(ref->d), lg, grid, s));
     unsigned long long hst[ST_COUNT] = {};
     if (opts.stats) {
         KNN_HIP(hipEventRecord(ev[1], s));

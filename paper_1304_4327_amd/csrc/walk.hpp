@@ -73,57 +73,106 @@ __device__ __forceinline__ void tree_walk(int first_leaf, Score &&score, Leaf &&
     }
 }
 
-// The same walk with every node scored exactly once (when its parent is
-// expanded): the decision for the second child is remembered per depth
-// instead of scored again on the way back.  For rules whose Score has an
-// effect (kernel density's approximation adds a contribution).
-template <class Score, class Leaf, class Order>
-__device__ __forceinline__ void tree_walk_once(int first_leaf, Score &&score, Leaf &&leaf,
-                                               Order &&right_first) {
-    float m0, m1;
-    if (!score(0, m0)) return;
-    int node = 0, depth = 0;
-    uint64_t firstbits = 0, secondbits = 0;
-    bool down = true;
+// The same walk for a Score that depends on the two boxes alone: five levels
+// below a node are scored at once, a node per lane, and the walk below it is
+// bit arithmetic on the ballots.  Lane v holds the descendant with heap index
+// v under the block's root (v = 1), which is node (root << level) + v - 1.
+// The second children still to be visited are bits of a mask; they are
+// siblings of the path's nodes, one a level, so the next one is the highest.
+// The first block takes the levels that are left over, so the last one is
+// full.  Nodes, and the two children of each, are visited in tree_walk's
+// order.
+//
+// score(node, on, keep, appr, key) : per lane, node of that lane (on: exists)
+// appr(node)    : wave-uniform, a visited node's approximation
+// leaf(node)    : wave-uniform, BaseCase
+// returns the number of nodes that the walk looked at
+template <class Score, class Appr, class Leaf>
+__device__ __forceinline__ uint32_t tree_walk_blocks(int first_leaf, Score &&score, Appr &&appr,
+                                                     Leaf &&leaf) {
+    constexpr int kLevels = 5;
+    const int lane = threadIdx.x & 63;
+    const int lane_level = 31 - __clz(lane | 1);
+    const int height = 31 - __clz(first_leaf + 1);
+    uint64_t keep = 0, ap = 0, right = 0, todo = 0;
+    auto block = [&](int root, int levels) {
+        const bool on = lane >= 1 && lane_level <= levels;
+        const int node = on ? (root << lane_level) + lane - 1 : 0;
+        bool k, p;
+        float key;
+        score(node, on, k, p, key);
+        keep = ballot(k);
+        ap = ballot(p);
+        // at the left child's bit: the right one is nearer
+        right = ballot(dpp_f<0xB1>(key) < key);
+    };
+    uint32_t n = 1;
+    int root = 0, levels = height % kLevels ? height % kLevels : min(height, kLevels);
+    block(0, levels);
+    if (ap & 2) appr(0);
+    if (!(keep & 2)) return n;
+    // the blocks above the current one, one a lane
+    int sp = 0, s_root = 0;
+    uint64_t s_keep = 0, s_ap = 0, s_right = 0, s_todo = 0;
+    int v = 1;
     for (;;) {
+        int node;
         bool at_leaf = false;
         for (;;) {
-            if (down) {
-                if (node >= first_leaf) {
-                    at_leaf = true;
-                    break;
-                }
-                const int c0 = 2 * node + 1, c1 = c0 + 1;
-                const bool k0 = score(c0, m0);
-                const bool k1 = score(c1, m1);
-                if (!k0 && !k1) {
-                    down = false;
-                    continue;
-                }
-                const bool right = k1 && (!k0 || right_first(m0, m1));
-                const bool second = right ? k0 : k1;
-                const uint64_t bit = uint64_t(1) << depth;
-                firstbits = right ? (firstbits | bit) : (firstbits & ~bit);
-                secondbits = second ? (secondbits | bit) : (secondbits & ~bit);
-                node = uniform_i(right ? c1 : c0);
-                ++depth;
+            const int level = 31 - __builtin_clz(v);
+            node = (root << level) + v - 1;
+            if (node >= first_leaf) {
+                at_leaf = true;
+                break;
+            }
+            if (level == levels) {
+                const bool here = lane == sp;
+                s_root = here ? root : s_root;
+                s_keep = here ? keep : s_keep;
+                s_ap = here ? ap : s_ap;
+                s_right = here ? right : s_right;
+                s_todo = here ? todo : s_todo;
+                ++sp;
+                root = node;
+                levels = kLevels;
+                todo = 0;
+                v = 1;
+                block(root, kLevels);
+            }
+            n += 2;
+            const int c0 = 2 * v;
+            const int a2 = int(ap >> c0) & 3, k2 = int(keep >> c0) & 3;
+            if (a2) {
+                if (a2 & 1) appr(2 * node + 1);
+                if (a2 & 2) appr(2 * node + 2);
+            }
+            if (k2 == 3) {
+                const int r = int(right >> c0) & 1;
+                v = c0 + r;
+                todo |= uint64_t(1) << (c0 + 1 - r);
+            } else if (k2) {
+                v = c0 + (k2 >> 1);
             } else {
-                if (node == 0) break;
-                --depth;
-                const bool is_right = (node & 1) == 0;
-                const bool first_right = (firstbits >> depth) & 1;
-                if (is_right == first_right && ((secondbits >> depth) & 1)) {
-                    node = uniform_i(is_right ? node - 1 : node + 1);
-                    ++depth;
-                    down = true;
-                    continue;
-                }
-                node = uniform_i((node - 1) >> 1);
+                break;
             }
         }
-        if (!at_leaf) break;
-        leaf(node);
-        down = false;
+        if (at_leaf) leaf(node);
+        while (todo == 0) {
+            if (sp == 0) return n;
+            --sp;
+            auto get = [&](uint64_t x) {
+                return uint64_t(uint32_t(__builtin_amdgcn_readlane(int(x), sp))) |
+                       uint64_t(uint32_t(__builtin_amdgcn_readlane(int(x >> 32), sp))) << 32;
+            };
+            root = __builtin_amdgcn_readlane(s_root, sp);
+            keep = get(s_keep);
+            ap = get(s_ap);
+            right = get(s_right);
+            todo = get(s_todo);
+            if (sp == 0) levels = height % kLevels ? height % kLevels : kLevels;
+        }
+        v = 63 - __builtin_clzll(todo);
+        todo &= ~(uint64_t(1) << v);
     }
 }
 
