@@ -129,31 +129,38 @@ k_search_far(const SearchArgs a) {
         return a.bound == KNN_BOUND_NONE ? 0.f : fmaxf(bound2, kth2());
     };
     // Score of a reference node: the lane keeps it unless the farthest point
-    // of its box is nearer than the lane's bound; the wave-uniform order key
-    // is d_max^2 between the union box and the node's box
-    auto score = [&](int node, float &key_out) -> bool {
+    // of its box is nearer than the lane's bound
+    auto score = [&](int node) -> bool {
         ++n_score;
         const float *b = a.rbox + int64_t(node) * 2 * DP;
-        float sd = 0.f, u = 0.f;
+        float sd = 0.f;
 #pragma unroll
         for (int j = 0; j < DP; ++j) {
-            const float lo = b[j], hi = b[DP + j];
-            const float s = fmaxf(fmaxf(q[j] - lo, hi - q[j]), 0.0f);
+            const float s = fmaxf(fmaxf(q[j] - b[j], b[DP + j] - q[j]), 0.0f);
             sd = fmaf(s, s, sd);
-            if constexpr (!WIDE) {
-                const float us = fmaxf(fmaxf(uhi[j] - lo, hi - ulo[j]), 0.0f);
+        }
+        const bool keep = valid && !(sd < point_bound2() * kShrink);
+        return ballot(keep) != 0;
+    };
+    // the wave-uniform order key, taken only where both children are kept (1M
+    // on 1M points, d = 3, k = 10: 1147 us with every score, 1117 so): d_max^2
+    // between the union box and the node's box
+    auto far_key = [&](int node) -> float {
+        const float *b = a.rbox + int64_t(node) * 2 * DP;
+        float u = 0.f;
+        if constexpr (!WIDE) {
+#pragma unroll
+            for (int j = 0; j < DP; ++j) {
+                const float us = fmaxf(fmaxf(uhi[j] - b[j], b[DP + j] - ulo[j]), 0.0f);
                 u = fmaf(us, us, u);
             }
-        }
-        if constexpr (WIDE) {
+        } else {
             const float lo = lane < DP ? b[lane] : 0.f, hi = lane < DP ? b[DP + lane] : 0.f;
             const float us = fmaxf(fmaxf(uhi[0] - lo, hi - ulo[0]), 0.0f);
             u = us * us;
             u = sum_dim_lanes<DP>(u);
         }
-        key_out = uniform_f(u);
-        const bool keep = valid && !(sd < point_bound2() * kShrink);
-        return ballot(keep) != 0;
+        return uniform_f(u);
     };
     auto insert = [&](float x, int id) { sorted_insert<K>(key, idx, x, id); };
     // L after a tile: min and max of the leaf's k-th distances, then the
@@ -224,10 +231,9 @@ k_search_far(const SearchArgs a) {
 
     // ---- stackless depth-first walk, farther child first --------------------
     {
-        float dm0, dm1;
         int node = 0, depth = 0;
         uint64_t firstbits = 0;
-        bool down = score(0, dm0);
+        bool down = score(0);
         if (down) {
             for (;;) {
                 bool leaf = false;
@@ -238,13 +244,13 @@ k_search_far(const SearchArgs a) {
                             break;
                         }
                         const int c0 = 2 * node + 1, c1 = c0 + 1;
-                        const bool k0 = score(c0, dm0);
-                        const bool k1 = score(c1, dm1);
+                        const bool k0 = score(c0);
+                        const bool k1 = score(c1);
                         if (!k0 && !k1) {
                             down = false;
                             continue;
                         }
-                        const bool right = k1 && (!k0 || dm1 > dm0);
+                        const bool right = k1 && (!k0 || far_key(c1) > far_key(c0));
                         if (right)
                             firstbits |= (uint64_t(1) << depth);
                         else
@@ -258,7 +264,7 @@ k_search_far(const SearchArgs a) {
                         const bool first_right = (firstbits >> depth) & 1;
                         if (is_right == first_right) {
                             const int other = is_right ? node - 1 : node + 1;
-                            if (score(other, dm0)) {
+                            if (score(other)) {
                                 node = other;
                                 ++depth;
                                 down = true;
