@@ -14,7 +14,12 @@
 //      atomic minimum.  (B2 stays a bound: a node holding two components
 //      holds an edge of length <= 2 lambda between them.)  Before the walk
 //      each point's nearest outside point from the previous round, when it
-//      is still outside, seeds its component's D;
+//      is still outside, seeds its component's D.
+//      Most points need no walk: the k-nearest-neighbour search lists each
+//      point's kNear nearest points once, and the first of them outside the
+//      component is the point's answer.  A point whose list is used up walks
+//      only if its list's reach (a lower bound of every other distance) is
+//      within its bound (k_near);
 //   3. every component's edge: the smallest of its points' candidates under
 //      the strict order (squared length, smaller index, larger index), taken
 //      in three atomic-minimum passes (length, then the two endpoints), so
@@ -31,6 +36,7 @@
 // length (products rounded, summed in dimension order).
 #include "walk.hpp"
 
+#include <algorithm>
 #include <cmath>
 #include <string>
 #include <vector>
@@ -51,6 +57,8 @@ struct EmstArgs {
     int bound;             // knn_bound
     int shared;            // 0 in the first round: every component is one
                            // point, whose own candidate is its bound
+    const float *need;     // with lists, per position: +inf if best_d2 and best_r
+                           // already hold its answer, else its list's reach
     unsigned long long *stats;
 };
 
@@ -84,6 +92,14 @@ __device__ inline bool run_min(int c, T v, bool act, T &m) {
     return act && (lane == 63 || knext != key);
 }
 
+// an atomic minimum that reads first: in late rounds most points share a few
+// components, whose words would take every run's atomic in turn (1M points,
+// d = 3: the slowest k_pick_len 68 us with plain atomics, 12 so)
+template <class T>
+__device__ inline void lower_to(T *word, T v) {
+    if (v < __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMin(word, v);
+}
+
 template <int DP, int LG>
 __global__ __launch_bounds__(256) void k_boruvka(const EmstArgs a) {
     constexpr float kInf = __builtin_inff();
@@ -111,9 +127,19 @@ __global__ __launch_bounds__(256) void k_boruvka(const EmstArgs a) {
     double best2 = __builtin_inf();
     int bpos = -1, bperm = 0x7fffffff;
     float pb = kInf;  // this point's bound, squared
+    // act: the point still takes part in the walk
+    bool act = valid;
+    float reach = 0.f;
+    if (a.need && valid) {
+        reach = a.need[qpos];
+        if (reach == kInf) {
+            act = false;
+            best2 = a.best_d2[qpos];
+            bpos = a.best_r[qpos];
+        }
+    }
     uint32_t n_score = 0, n_tiles = 0;
     uint64_t n_pairs = 0;
-    const int n_valid = __popcll(ballot(valid));
 
     // D_p = min(own candidate, the component's shared bound); the leaf's
     // B(N_q) = min(max D_p, min D_p + 2 lambda); the point's bound is
@@ -137,6 +163,7 @@ __global__ __launch_bounds__(256) void k_boruvka(const EmstArgs a) {
             b = fminf(b, t * t);
         }
         pb = fminf(dp, b);
+        act = act && !(reach > pb);
     };
     refresh();
     auto score = [&](int node, float &key) -> bool {
@@ -146,7 +173,7 @@ __global__ __launch_bounds__(256) void k_boruvka(const EmstArgs a) {
         box_dist2<DP>(q, a.box + int64_t(node) * 2 * DP, dmin2, dmax2);
         key = uniform_f(dmin2);
         if (nc == -2) return false;
-        const bool keep = valid && nc != c && !(dmin2 > pb * kSlack);
+        const bool keep = act && nc != c && !(dmin2 > pb * kSlack);
         return ballot(keep) != 0;
     };
     constexpr int CH = DP >= 32 ? 1 : 32 / DP;
@@ -156,7 +183,7 @@ __global__ __launch_bounds__(256) void k_boruvka(const EmstArgs a) {
         const int base = uniform_i(rr.x);
         const int cnt = uniform_i(rr.y);
         const float *rp = a.lpts + int64_t(node - a.first_leaf) * a.leaf_slots * DP;
-        n_pairs += uint64_t(cnt) * uint64_t(n_valid);
+        n_pairs += uint64_t(cnt) * uint64_t(__popcll(ballot(act)));
         bool improved = false;
         // the filter follows the best candidate within the leaf too
         float thr = pb * kGamma;
@@ -171,7 +198,7 @@ __global__ __launch_bounds__(256) void k_boruvka(const EmstArgs a) {
                     const float df = q[j] - rp[t * DP + j];
                     sd = fmaf(df, df, sd);
                 }
-                const bool cand = valid && rc != c && sd <= thr;
+                const bool cand = act && rc != c && sd <= thr;
                 if (cand) {
                     const double x = d2_fp64_unfused<DP>(q, rp + t * DP);
                     const int ro = a.perm[base + t];
@@ -246,12 +273,20 @@ __global__ void k_leaf_comp(const int2 *range, const int32_t *comp, int first_le
     }
     node_comp[first_leaf + l] = lab;
 }
-__global__ void k_level_comp(int32_t *node_comp, int first, int count) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= count) return;
-    const int node = first + i;
+__device__ inline void join_comp(int32_t *node_comp, int node) {
     const int x = node_comp[2 * node + 1], y = node_comp[2 * node + 2];
     node_comp[node] = x == -2 ? y : (y == -2 ? x : (x == y ? x : -1));
+}
+__global__ void k_level_comp(int32_t *node_comp, int first, int count) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < count) join_comp(node_comp, first + i);
+}
+// the levels of up to 1024 nodes in one workgroup: ten launches fewer a round
+__global__ __launch_bounds__(1024) void k_top_comp(int32_t *node_comp, int level) {
+    for (int l = level; l >= 0; --l) {
+        if (int(threadIdx.x) < (1 << l)) join_comp(node_comp, (1 << l) - 1 + threadIdx.x);
+        __syncthreads();
+    }
 }
 
 __global__ void k_round_reset(unsigned int *cbound, unsigned long long *cbest, unsigned int *cmin,
@@ -275,24 +310,137 @@ __global__ void k_seed_bounds(const double *best_d2, const int32_t *best_r, cons
     const int c = i < n ? comp[i] : 0;
     const bool act = r >= 0 && comp[r] != c;
     unsigned int m;
-    if (run_min(c, act ? f32_bits_up(best_d2[i]) : ~0u, act, m)) atomicMin(&cbound[c], m);
+    if (run_min(c, act ? f32_bits_up(best_d2[i]) : ~0u, act, m)) lower_to(&cbound[c], m);
+}
+
+// Neighbour lists.  kNear = 10: of a uniform or clustered set at d = 3 under
+// 3% of the wavefronts then hold a point that has to walk, until whole
+// clusters are left (28% with 8 neighbours, none with 16).  1M points, d = 3:
+// 9.5 ms without lists, 4.80 with 8, 4.78 with 10, 5.6 with 16.  Used at
+// strides up to 8 from kNearPoints points on (ms without and with lists: 2048
+// points 1.30 and 1.02, 30,000 2.41 and 1.49 at d = 3; 100,000 2.05 and 1.57
+// at d = 2, 10.2 and 5.4 at d = 8; 600,000 22.8 and 9.3 at d = 5).  The
+// padding dimensions add exact zeros to the squared lengths.
+constexpr int kNear = 10;
+constexpr int64_t kNearPoints = 2048;
+
+__global__ void k_inverse(const int32_t *perm, int32_t *inv, int n) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < n) inv[perm[i]] = i;
+}
+
+// One point's list from the search's output: tree positions in the order of
+// (FP64 squared length, index), cut at the reach: every point that is not
+// listed is at least as far.  The search decides on FP32 distances, each
+// within (d + 3) 2^-24 of its value as long as it is far from FP32's limits;
+// the reach lies 2^-14 below the last one, and is 0 (nothing listed) where it
+// may not be.
+template <int DP>
+__global__ void k_near_lists(const float *pts, const int32_t *perm, const int32_t *inv,
+                             const int64_t *idx, const float *dist, int32_t *near, float *reach,
+                             int n) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= n) return;
+    float q[DP];
+#pragma unroll
+    for (int j = 0; j < DP; ++j) q[j] = pts[int64_t(i) * DP + j];
+    const int64_t row = int64_t(perm[i]) * kNear;
+    const double last = dist[row + kNear - 1], l2 = last * last;
+    const float lim = l2 > 1e-30 && l2 < 1e37 ? float(l2 * (1.0 - 0x1p-14)) : 0.f;
+    double x[kNear];
+    int id[kNear], pos[kNear];
+#pragma unroll
+    for (int j = 0; j < kNear; ++j) {
+        id[j] = int(idx[row + j]);
+        pos[j] = inv[id[j]];
+        x[j] = d2_fp64_unfused<DP>(q, pts + int64_t(pos[j]) * DP);
+        if (!(x[j] < double(lim))) {
+            x[j] = __builtin_inf();
+            pos[j] = -1;
+        }
+    }
+    // odd-even transposition: kNear rounds sort kNear entries
+#pragma unroll
+    for (int r = 0; r < kNear; ++r)
+#pragma unroll
+        for (int j = r & 1; j + 1 < kNear; j += 2)
+            if (x[j + 1] < x[j] || (x[j + 1] == x[j] && id[j + 1] < id[j])) {
+                const double tx = x[j];
+                const int ti = id[j], tp = pos[j];
+                x[j] = x[j + 1];
+                id[j] = id[j + 1];
+                pos[j] = pos[j + 1];
+                x[j + 1] = tx;
+                id[j + 1] = ti;
+                pos[j + 1] = tp;
+            }
+#pragma unroll
+    for (int j = 0; j < kNear; ++j) near[int64_t(j) * n + i] = pos[j];
+    reach[i] = lim;
+}
+
+// Start of a round with lists: the first listed point outside the component
+// is the point's nearest one (at[i]: entries before it are inside for good);
+// where none is left, need is the reach, and last round's nearest outside
+// point still bounds the component (k_seed_bounds).
+template <int DP>
+__global__ void k_near(const float *pts, const int32_t *near, const float *reach, uint8_t *at,
+                       const int32_t *comp, double *best_d2, int32_t *best_r, float *need,
+                       unsigned int *cbound, int first, int n) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    const int c = i < n ? comp[i] : 0;
+    int r = -1;
+    double x = 0.0;
+    if (i < n) {
+        int j = first ? 0 : at[i];
+        for (; j < kNear; ++j) {
+            r = near[int64_t(j) * n + i];
+            if (r < 0) j = kNear;
+            else if (comp[r] != c) break;
+            else r = -1;
+        }
+        at[i] = uint8_t(min(j, kNear));
+        if (r >= 0) {
+            float q[DP];
+#pragma unroll
+            for (int k = 0; k < DP; ++k) q[k] = pts[int64_t(i) * DP + k];
+            x = d2_fp64_unfused<DP>(q, pts + int64_t(r) * DP);
+            best_d2[i] = x;
+            best_r[i] = r;
+            need[i] = __builtin_inff();
+        } else {
+            need[i] = reach[i];
+            if (!first) {
+                r = best_r[i];
+                if (r >= 0 && comp[r] == c) r = -1;
+                if (r >= 0) x = best_d2[i];
+            }
+        }
+    }
+    if (first) return;
+    unsigned int m;
+    if (run_min(c, r >= 0 ? f32_bits_up(x) : ~0u, r >= 0, m)) lower_to(&cbound[c], m);
 }
 
 // the component's edge: smallest (length, smaller index, larger index).
 // In the first round every component is one point (labels are the points'
 // own positions): a plain store
 __device__ inline unsigned long long dbits(double x) { return (unsigned long long)__double_as_longlong(x); }
+// Later only a point within its component's bound can hold the edge.
 __global__ void k_pick_len(const double *best_d2, const int32_t *best_r, const int32_t *comp,
-                           unsigned long long *cbest, int n, int singletons) {
+                           const unsigned int *cbound, unsigned long long *cbest, int n,
+                           int singletons) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    const bool act = i < n && best_r[i] >= 0;
+    bool act = i < n && best_r[i] >= 0;
     if (singletons) {
         if (act) cbest[i] = dbits(best_d2[i]);
         return;
     }
     const int c = i < n ? comp[i] : 0;
+    const double x = act ? best_d2[i] : 0.0;
+    act = act && f32_bits_up(x) <= cbound[c];
     unsigned long long m;
-    if (run_min(c, act ? dbits(best_d2[i]) : ~0ull, act, m)) atomicMin(&cbest[c], m);
+    if (run_min(c, act ? dbits(x) : ~0ull, act, m)) lower_to(&cbest[c], m);
 }
 __global__ void k_pick_ends(const double *best_d2, const int32_t *best_r, const int32_t *comp,
                             const int32_t *perm, const unsigned long long *cbest,
@@ -492,19 +640,66 @@ extern "C" knn_status knn_emst(const knn_tree *t, const knn_opts *opts_in, int64
         KNN_HIP(hipEventCreate(&ev1));
         KNN_HIP(hipEventRecord(ev0, s));
     }
+    // the neighbour lists; without the memory for them every point walks
+    int32_t *near = nullptr;
+    float *reach = nullptr, *need = nullptr;
+    uint8_t *at = nullptr;
+    knn_stats searched{};
+    if (opts.bound != KNN_BOUND_NONE && n >= kNearPoints && t->dp <= 8) {
+        int64_t *idx = nullptr;
+        float *dist = nullptr;
+        int32_t *inv = nullptr;
+        const size_t keep = held.size();
+        const bool room = get(&near, size_t(n) * kNear) == hipSuccess && get(&reach, n) == hipSuccess &&
+                          get(&need, n) == hipSuccess && get(&at, n) == hipSuccess;
+        const size_t temp = held.size();
+        knn_status st = KNN_E_OOM;
+        if (room && get(&idx, size_t(n) * kNear) == hipSuccess &&
+            get(&dist, size_t(n) * kNear) == hipSuccess && get(&inv, n) == hipSuccess) {
+            knn_opts o;
+            knn_opts_default(&o);
+            o.exclude_self = 1;
+            o.stats = opts.stats ? &searched : nullptr;
+            st = knn_search(t, nullptr, kNear, &o, idx, dist, stream);
+        }
+        if (st == KNN_OK) {
+            k_inverse<<<blocks(n), 256, 0, s>>>(t->perm, inv, n);
+            auto kern = t->dp == 4 ? k_near_lists<4> : k_near_lists<8>;
+            kern<<<blocks(n), 256, 0, s>>>(t->pts, t->perm, inv, idx, dist, near, reach, n);
+            KNN_HIP(hipGetLastError());
+            a.need = need;
+        } else if (st == KNN_E_OOM) {
+            (void)hipGetLastError();
+            set_error("");
+        } else {
+            return st;
+        }
+        const size_t drop = a.need ? temp : keep;
+        dev_free_many(held.data() + drop, int(held.size() - drop), s);
+        held.resize(drop);
+    }
     int edges = 0, rounds = 0;
     while (edges < n - 1) {
         if (++rounds > 64) return fail(KNN_E_DEVICE, w + ": no progress after 64 rounds");
         k_leaf_comp<<<blocks(a.n_leaves), 256, 0, s>>>(t->range, comp, a.first_leaf, a.n_leaves,
                                                       node_comp);
-        for (int l = t->depth - 1; l >= 0; --l)
+        for (int l = t->depth - 1; l > 10; --l)
             k_level_comp<<<blocks(1 << l), 256, 0, s>>>(node_comp, (1 << l) - 1, 1 << l);
+        if (t->depth > 0)
+            k_top_comp<<<1, 1024, 0, s>>>(node_comp, std::min(t->depth - 1, 10));
         k_round_reset<<<blocks(n), 256, 0, s>>>(cbound, cbest, cmin, cmax, parent, count + 1, n);
-        if (rounds > 1) k_seed_bounds<<<blocks(n), 256, 0, s>>>(best_d2, best_r, comp, cbound, n);
+        if (a.need) {
+            auto kern = t->dp == 4 ? k_near<4> : k_near<8>;
+            kern<<<blocks(n), 256, 0, s>>>(t->pts, near, reach, at, comp, best_d2, best_r, need,
+                                           cbound, rounds == 1 ? 1 : 0, n);
+        } else if (rounds > 1) {
+            k_seed_bounds<<<blocks(n), 256, 0, s>>>(best_d2, best_r, comp, cbound, n);
+        }
         KNN_HIP(hipGetLastError());
         a.shared = rounds > 1 ? 1 : 0;
         KNN_HIP(launch_dp(a, t->dp, lg, grid, s));
-        k_pick_len<<<blocks(n), 256, 0, s>>>(best_d2, best_r, comp, cbest, n, rounds == 1 ? 1 : 0);
+        k_pick_len<<<blocks(n), 256, 0, s>>>(best_d2, best_r, comp, cbound, cbest, n,
+                                             rounds == 1 ? 1 : 0);
         k_pick_ends<<<blocks(n), 256, 0, s>>>(best_d2, best_r, comp, t->perm, cbest, cmin, cmax, 0, n);
         k_pick_ends<<<blocks(n), 256, 0, s>>>(best_d2, best_r, comp, t->perm, cbest, cmin, cmax, 1, n);
         k_hook<<<blocks(n), 256, 0, s>>>(best_d2, best_r, comp, t->perm, cbest, cmin, cmax, parent,
@@ -536,9 +731,9 @@ extern "C" knn_status knn_emst(const knn_tree *t, const knn_opts *opts_in, int64
     if (rounds_out) *rounds_out = rounds;
     if (opts.stats) {
         knn_stats *st = opts.stats;
-        st->score_calls = int64_t(hst[ST_SCORE]);
-        st->leaf_tiles = int64_t(hst[ST_TILES]);
-        st->pairs = int64_t(hst[ST_PAIRS]);
+        st->score_calls = int64_t(hst[ST_SCORE]) + searched.score_calls;
+        st->leaf_tiles = int64_t(hst[ST_TILES]) + searched.leaf_tiles;
+        st->pairs = int64_t(hst[ST_PAIRS]) + searched.pairs;
         st->n_query_leaves = a.n_leaves;
         (void)hipEventElapsedTime(&st->ms_search, ev0, ev1);
         st->ms_main_kernel = st->ms_search;
