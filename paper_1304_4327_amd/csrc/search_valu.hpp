@@ -6,10 +6,13 @@
 //   * a wavefront owns NG = 64 / LPL consecutive query leaves (LPL = lanes per
 //     leaf, a power of two >= the largest leaf); lane = one query point;
 //   * it walks the reference tree depth first, nearer child first (the
-//     closer-of / farther-of order of Gray's AllNN, Algorithm 4), without a
-//     stack: one bit per depth records which child was entered first, and the
-//     farther child is re-scored when the walk climbs back (bounds only
-//     tighten, so the re-score can only prune more);
+//     closer-of / farther-of order of Gray's AllNN, Algorithm 4).  The plain
+//     form at d <= 8 and with matrix-core tiles at d <= 16 takes the order
+//     keys of five levels at once, a node per lane, and scores a node where it
+//     enters it; the others keep one bit per depth for the child entered
+//     first, score both children of a node and re-score the farther one when
+//     the walk climbs back (bounds only tighten, so a later score can only
+//     prune more, and both reach the same leaves in the same order);
 //   * Score: each query point is scored as a singleton child of its leaf, so
 //     N_q = {p}, d_min(N_q, N_r) = distance from p to the node's box, and
 //     B(N_q) = min(D_p[k], B(leaf)) (B1({p}) = D_p[k], lambda = 0, and the
@@ -132,6 +135,14 @@ __device__ __forceinline__ void search_valu_body(const SearchArgs &a) {
     // several waves may share a slot (split_for); up to stride 16 few queries
     // go to the one-query-per-wave kernel instead
     constexpr bool SPLIT = D >= 32 && MODE == kValuPlain;
+    // the walk by blocks of five levels (below).  ms before and with it, k = 10
+    // unless said: 1M points d = 2 0.43 and 0.41, d = 3 1.71 and 1.67 (k = 3
+    // 0.67 and 0.58), d = 4 1.96 and 1.90; 600,000 at k = 20 d = 5 8.4 and 7.6,
+    // d = 8 21.3 and 18.9; matrix-core tiles 2M points d = 8 58.0 and 50.4, 4M
+    // of 1M d = 16 14.2 and 13.3, 150,000 d = 13 k = 7 1.33 and 1.21.  The
+    // plain form at stride 16 has no registers for it (400,000, k = 20 5.4 and
+    // 6.6), the seeded and debug forms keep the walk that scores both children.
+    constexpr bool BLOCKS = MODE == kValuPlain && D <= (MT ? 16 : 8);
     constexpr float kInf = __builtin_inff();
     constexpr float kSlack = 1.0f + 0x1p-16f;            // prune slack (squared)
     constexpr float kGamma = 1.0f + (D + 6) * 0x1p-24f;  // FP32 filter slack
@@ -654,7 +665,155 @@ __device__ __forceinline__ void search_valu_body(const SearchArgs &a) {
     // (a loop of at most two passes around the walk: as a closure called
     // twice, the walk made the kernel much slower)
     for (int pass = 0;; ++pass) {
-        if (!replay) {
+        if constexpr (BLOCKS) {
+            // The same leaves in the same order, with the visit-order keys of
+            // the 62 nodes below a node taken at once, a node per lane.  Lane v
+            // holds the descendant with heap index v under the block's root
+            // (v = 1), which is node (root << level) + v - 1; the second
+            // children still to be visited are bits of todo, siblings of the
+            // path's nodes, one a level, so the next one is the highest.  A
+            // node is scored once, where the walk would enter it (the bounds
+            // only shrink, so a node that an earlier Score would have dropped
+            // is dropped then); nodes whose box misses every bound of the
+            // wave from the union of its leaves are left out with the keys.
+            // The first block takes the levels left over.
+            constexpr int kLevels = 5;
+            const int lane_level = 31 - __clz(lane | 1);
+            const int height = 31 - __builtin_clz(a.r_first_leaf + 1);
+            const int top_levels = height % kLevels ? height % kLevels : min(height, kLevels);
+            uint64_t keep = 0, right = 0, todo = 0;
+            auto block = [&](int root, int n_levels) {
+#pragma clang fp contract(off)
+                const bool on = lane >= 1 && lane_level <= n_levels;
+                const float *b = a.rbox + int64_t(on ? (root << lane_level) + lane - 1 : 0) * 2 * DP;
+                float e[D];
+#pragma unroll
+                for (int j = 0; j < D; ++j) {
+                    float lo, hi;
+                    if constexpr (WIDE) {
+                        lo = __builtin_bit_cast(
+                            float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, ulo[0]), j));
+                        hi = __builtin_bit_cast(
+                            float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, uhi[0]), j));
+                    } else {
+                        lo = ulo[j];
+                        hi = uhi[j];
+                    }
+                    e[j] = fmaxf(fmaxf(b[j] - hi, lo - b[DP + j]), 0.0f);
+                }
+                // the sums of box_key
+                float key = 0.f;
+                if constexpr (WIDE) {
+#pragma unroll
+                    for (int j = 0; j < D; ++j) e[j] = e[j] * e[j];
+#pragma unroll
+                    for (int st = 1; st < D; st <<= 1)
+#pragma unroll
+                        for (int j = 0; j < D; j += 2 * st) e[j] = e[j] + e[j + st];
+                    key = e[0];
+                } else {
+#pragma unroll
+                    for (int j = 0; j < D; ++j) key = fmaf(e[j], e[j], key);
+                }
+                float most = valid ? point_bound2() : -kInf;
+#pragma unroll
+                for (int l = 0; l < 6; ++l) most = xor_level(most, l, OpMax());
+                keep = ballot(on && !(key > most * kSlack));
+                // at the left child's bit: the right one is nearer
+                right = ballot(dpp_f<0xB1>(key) < key);
+            };
+            // Score where the walk enters a node; its children's boxes (and,
+            // if they are leaves, their first rows) are touched with its own
+            auto enter = [&](int node) -> bool {
+                ++n_score;
+                const bool inner = node < a.r_first_leaf;
+                const float *g = inner ? a.rbox + int64_t(2 * node + 1) * 2 * DP
+                                       : a.rbox + int64_t(node) * 2 * DP;
+                const uint32_t p0 = __float_as_uint(g[0]);
+                uint32_t p1 = 0, p2 = 0;
+                if (inner) {
+                    p1 = __float_as_uint(g[DP == 4 ? 15 : 16]);
+                    if constexpr (DP == 16) p2 = __float_as_uint(g[32]) ^ __float_as_uint(g[48]);
+                    if (!MT && 2 * node + 1 >= a.r_first_leaf) {
+                        const float *r =
+                            a.rlpts + int64_t(2 * node + 1 - a.r_first_leaf) * a.r_leaf_slots * DP;
+                        p2 = __float_as_uint(r[0]) ^ __float_as_uint(r[a.r_leaf_slots * DP]);
+                    }
+                }
+                const bool kept = score_box(a.rbox + int64_t(node) * 2 * DP);
+                tacc ^= q0 ^ q1 ^ q2;
+                q0 = p0;
+                q1 = p1;
+                q2 = p2;
+                return kept;
+            };
+            // the blocks above the current one, one a lane
+            int sp = 0, s_root = 0;
+            uint64_t s_keep = 0, s_right = 0, s_todo = 0;
+            int root = 0, n_levels = top_levels, v = 1, node = 0;
+            // to the next node to visit; false when there is none
+            auto next = [&]() -> bool {
+                while (todo == 0) {
+                    if (sp == 0) return false;
+                    --sp;
+                    auto get = [&](uint64_t x) {
+                        return uint64_t(uint32_t(__builtin_amdgcn_readlane(int(x), sp))) |
+                               uint64_t(uint32_t(__builtin_amdgcn_readlane(int(x >> 32), sp))) << 32;
+                    };
+                    root = __builtin_amdgcn_readlane(s_root, sp);
+                    keep = get(s_keep);
+                    right = get(s_right);
+                    todo = get(s_todo);
+                    if (sp == 0) n_levels = top_levels;
+                }
+                v = 63 - __builtin_clzll(todo);
+                todo &= ~(uint64_t(1) << v);
+                return true;
+            };
+            block(0, n_levels);
+            for (bool more = true; more;) {
+                bool leaf = false;
+                for (;;) {
+                    const int level = 31 - __builtin_clz(v);
+                    node = (root << level) + v - 1;
+                    if (enter(node)) {
+                        if (node >= a.r_first_leaf) {
+                            leaf = true;
+                            break;
+                        }
+                        if (level == n_levels) {
+                            const bool here = lane == sp;
+                            s_root = here ? root : s_root;
+                            s_keep = here ? keep : s_keep;
+                            s_right = here ? right : s_right;
+                            s_todo = here ? todo : s_todo;
+                            ++sp;
+                            root = node;
+                            n_levels = kLevels;
+                            todo = 0;
+                            v = 1;
+                            block(root, kLevels);
+                        }
+                        const int c0 = 2 * v;
+                        const int k2 = int(keep >> c0) & 3;
+                        if (k2 == 3) {
+                            const int r = int(right >> c0) & 1;
+                            v = c0 + r;
+                            todo |= uint64_t(1) << (c0 + 1 - r);
+                            continue;
+                        }
+                        if (k2) {
+                            v = c0 + (k2 >> 1);
+                            continue;
+                        }
+                    }
+                    if (!next()) break;
+                }
+                if (!leaf) break;
+                tile(node);
+                more = next();
+            }
+        } else if (!replay) {
             float dm0 = 0.f, dm1 = 0.f;
             int node = 0, depth = 0;
             uint64_t nearbits = 0;

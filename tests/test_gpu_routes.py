@@ -91,3 +91,23 @@ def test_fp32_sweep_equals_the_walk(n_ref, n_q, leaf, k, d, kind):
         x = ref if q is None else q
         oi, od = ok.knn_rows(x, rows, ref, k, exclude_self=q is None)
         parity.assert_ok(x, ref, k, got[0].cpu().numpy(), got[1].cpu().numpy(), oi, od, rows=rows)
+
+
+# the walk's blocks of five levels: trees of 0 to 11 levels, so that the first
+# block has every size; with counters the slot-per-wave walk serves the call
+@pytest.mark.parametrize("levels", [0, 1, 2, 3, 4, 5, 6, 9, 10, 11])
+@pytest.mark.parametrize("d,leaf,k", [(1, 1, 3), (3, 2, 10), (4, 32, 5), (8, 32, 10), (8, 7, 20),
+                                      (12, 32, 4), (16, 24, 15)])
+def test_walk_blocks_of_every_height(levels, d, leaf, k):
+    import torch
+    from paper_1304_4327_amd import knn
+    n = max(k + 1, (leaf << levels) - 1)
+    if n > 40_000:
+        n = 40_000
+    for kind in ("random", "twice"):
+        ref, q = _points(kind, n, d, n + d), _points(kind, 300, d, d)
+        rt, qt = _trees(ref, q, leaf)
+        walk = knn.knn_search(rt, qt, k, stats=True)
+        few = knn.knn_search(rt, qt, k)
+        torch.cuda.synchronize()
+        assert torch.equal(walk[0], few[0]) and torch.equal(walk[1], few[1])
