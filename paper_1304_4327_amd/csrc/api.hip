@@ -196,8 +196,8 @@ knn_status search(const knn_tree *ref, const knn_tree *query, int k, const knn_o
     // FP32 at strides 8 and 16: the same kernel where the plain form would take
     // two leaves a wave too (the visit order depends on the slot); it returns
     // what that form returns: 2M queries of 2M points at d = 8, k = 10 67 ms
-    // plain, 54 here; 150,000 points on themselves at d = 13, k = 7 1.72 ms
-    // plain, 1.31 here.  The seeded form stays plain.
+    // plain, 50 here; 150,000 points on themselves at d = 13, k = 7 1.72 ms
+    // plain, 1.21 here.  The seeded form stays plain.
     const bool mt32 = !bf16 && !dbg && !opts.seed_radius && (ref->dp == 8 || ref->dp == 16) &&
                       lpl_log2 == 5 && ref->leaf_slots <= 32 && K <= 16;
     const int NG = 64 >> lpl_log2;
@@ -209,12 +209,18 @@ knn_status search(const knn_tree *ref, const knn_tree *query, int k, const knn_o
 
     const int waves = (nq_leaves + NG - 1) / NG;
     const char *wlog_path = arena ? nullptr : std::getenv("KNN_WAVE_LOG");
-    // stride 64: the sweep with two query leaves per wave, for either
-    // precision (it returns what the FP32 walk returns; see walk_ties).  Not
-    // for the no-alloc form (its operands take 4 KB per reference leaf), nor
-    // for a seeded FP32 search, whose second pass runs inside the walk.
-    const bool pair = ref->dp == 64 && !arena && !dbg && max_leaf <= 32 && ref->leaf_slots <= 32 &&
-                      (bf16 || !opts.seed_radius);
+    // stride 64, and FP32 at stride 32: the sweep with two query leaves per
+    // wave (it returns what the FP32 walk returns; see walk_ties; BF16 requests
+    // at stride 32 have the walk with matrix-core tiles).  Not for the no-alloc
+    // form (its operands take 64 bytes per padded dimension and reference leaf),
+    // nor for a seeded FP32 search, whose second pass runs inside the walk.
+    // FP32 at stride 32, ms with the walk and with the sweep: 34,155 queries of
+    // 83,781 points (d = 32, k = 10) 34.1 and 2.0, 1000 of 3000 (d = 24) 1.01
+    // and 0.36, 100,000 of 1M (d = 32) 217 and 14.3; of a 4-dimensional manifold
+    // 200,000 of 500,000 (d = 24) 7.0 and 3.5; a mixture, 300,000 of 300,000
+    // (d = 18, k = 3) 26.9 and 8.1.
+    const bool pair = (ref->dp == 64 || (ref->dp == 32 && !bf16)) && !arena && !dbg &&
+                      max_leaf <= 32 && ref->leaf_slots <= 32 && (bf16 || !opts.seed_radius);
     // what only a slot-per-wave walk can do: its counters describe whole query
     // leaves, and a leaf's second pass and largest k-th distance need the
     // leaf's queries in one wave
@@ -326,15 +332,15 @@ knn_status search(const knn_tree *ref, const knn_tree *query, int k, const knn_o
         const size_t pl = size_t((nl + kSweepBlock - 1) / kSweepBlock) * kSweepBlock;  // padded leaves
         uint16_t *abf = nullptr, *cbf = nullptr;
         float *rn = nullptr, *rlen = nullptr, *cn = nullptr, *lam = nullptr, *bcen = nullptr, *rcb = nullptr;
-        KNN_HIP(sc.get(&abf, pl * 32 * 64));
+        KNN_HIP(sc.get(&abf, pl * 32 * ref->dp));
         KNN_HIP(sc.get(&rn, pl * 32));
         KNN_HIP(sc.get(&rlen, pl));
-        KNN_HIP(sc.get(&cbf, pl * 64));
+        KNN_HIP(sc.get(&cbf, pl * ref->dp));
         KNN_HIP(sc.get(&cn, pl));
         KNN_HIP(sc.get(&lam, pl));
-        KNN_HIP(sc.get(&bcen, pl / kSweepBlock * 64));
+        KNN_HIP(sc.get(&bcen, pl / kSweepBlock * ref->dp));
         KNN_HIP(sc.get(&rcb, pl / kSweepBlock));
-        KNN_HIP(launch_wsweep_prep(a, abf, rn, rlen, cbf, cn, lam, bcen, rcb, s));
+        KNN_HIP(launch_wsweep_prep(a, ref->dp, abf, rn, rlen, cbf, cn, lam, bcen, rcb, s));
         a.sw_abf = abf;
         a.sw_rn = rn;
         a.sw_rlen = rlen;
@@ -358,9 +364,13 @@ knn_status search(const knn_tree *ref, const knn_tree *query, int k, const knn_o
         for (auto &e : ev) KNN_HIP(hipEventCreate(&e));
         KNN_HIP(hipEventRecord(ev[0], s));
     }
+    auto launch_pair = [&](const SearchArgs &x) {
+        const int kk = k + (opts.exclude_self ? 1 : 0);
+        return ref->dp == 64 ? launch_search_pair_dp64(x, kk, s) : launch_search_pair_dp32(x, kk, s);
+    };
     KNN_HIP(dbg    ? launch_search_valu_debug_d3(a, K, grid, s)
             : few  ? launch_search_few_d(a, ref->d, qt->n, s)
-            : pair ? launch_search_pair_dp64(a, k + (opts.exclude_self ? 1 : 0), s)
+            : pair ? launch_pair(a)
             : mt32 && ref->dp == 8 ? launch_search_mt_d8(a, K, grid, s)
             : mt || mt32 ? (ref->dp == 16 ? launch_search_mt_d16(a, K, grid, s)
                                     : launch_search_mt_d32(a, K, grid, s))
@@ -381,7 +391,7 @@ knn_status search(const knn_tree *ref, const knn_tree *query, int k, const knn_o
         b.active = fb_flag;
         b.stats = dstats ? dstats + ST_COUNT : nullptr;  // counted separately
         b.wave_log = nullptr;
-        KNN_HIP(pair ? launch_search_pair_dp64(b, k + (opts.exclude_self ? 1 : 0), s)
+        KNN_HIP(pair ? launch_pair(b)
                      : launch_mfma(b, ref->dp, K, grid, s));
     }
     if (timing) KNN_HIP(hipEventRecord(ev[2], s));

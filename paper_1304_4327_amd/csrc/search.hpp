@@ -154,6 +154,7 @@ inline int pair_grid(int n_leaves, bool parts) {
 }
 // (256 CUs, two workgroups on each)
 inline bool pair_parts(int n_leaves) { return pair_grid(n_leaves, false) <= 256; }
+hipError_t launch_search_pair_dp32(const SearchArgs &a, int kk, hipStream_t s);
 hipError_t launch_search_pair_dp64(const SearchArgs &a, int kk, hipStream_t s);
 
 // reference leaves the d = 64 sweep scores together (one subtree)
@@ -162,7 +163,7 @@ constexpr int kSweepBlock = 32;
 // reference-side operands of the wave-independent d = 64 sweep (see the
 // sw_* fields): fills them for the n_blocks * 32 (padded) leaves of the
 // reference tree in args
-hipError_t launch_wsweep_prep(const SearchArgs &args, uint16_t *abf, float *rn, float *rlen,
+hipError_t launch_wsweep_prep(const SearchArgs &args, int dp, uint16_t *abf, float *rn, float *rlen,
                               uint16_t *cbf, float *cn, float *lam, float *bcen, float *rcb,
                               hipStream_t s);
 

@@ -8,8 +8,9 @@ namespace {
 
 // One workgroup per block of 32 reference leaves (the subtree whose leaves
 // the sweep scores together), four leaves at a time: thread t of a leaf's
-// 256 takes row t / 8, dimensions 8 (t % 8) .. + 7 (chunk c = 2 s + h of the
-// operand layout), so that reads and writes are whole 16-byte pieces.
+// 4 DP takes row t / (DP / 8), dimensions 8 c .. + 7 of chunk c = t % (DP / 8)
+// (c = 2 s + h of the operand layout), so that reads and writes are whole
+// 16-byte pieces.
 // Everything is centred on the block's box centre C_B = (lo + hi) / 2 of the
 // block's subtree node, the same FP32 value the search reads back from bcen.
 // Norms are FP32 sums of the FP32 differences in a fixed order (chunk, then
@@ -17,12 +18,13 @@ namespace {
 constexpr int kMebSteps = 32;  // enclosing-ball steps per leaf
 
 template <int DP>
-__global__ __launch_bounds__(1024) void k_wsweep_prep(const SearchArgs a, uint16_t *__restrict__ abf,
+__global__ __launch_bounds__(16 * DP) void k_wsweep_prep(const SearchArgs a, uint16_t *__restrict__ abf,
                                                       float *__restrict__ rn, float *__restrict__ rlen,
                                                       uint16_t *__restrict__ cbf, float *__restrict__ cn,
                                                       float *__restrict__ lam, float *__restrict__ bcen,
                                                       float *__restrict__ rcb) {
-    static_assert(DP == 64, "the operand layout below assumes 64 dimensions (8 chunks of 8)");
+    static_assert(DP == 64 || DP == 32, "8 or 4 chunks of 8 dimensions");
+    constexpr int TL = 4 * DP, CHUNKS = DP / 8;  // threads per leaf, chunks per row
     constexpr int NB = kSweepBlock;
     constexpr float kInf = __builtin_inff();
     __shared__ float s_cb[DP];
@@ -34,8 +36,8 @@ __global__ __launch_bounds__(1024) void k_wsweep_prep(const SearchArgs a, uint16
     __shared__ uint32_t s_max;      // the block: largest centre norm (bits)
     const int rb = blockIdx.x;
     const int tid = threadIdx.x;
-    const int ls = tid >> 8, t = tid & 255;
-    const int i = t >> 3, c = t & 7;
+    const int ls = tid / TL, t = tid % TL;
+    const int i = t / CHUNKS, c = t % CHUNKS;
     const int nl = a.r_first_leaf + 1;
     const int n_blocks = (nl + NB - 1) / NB;
     const int bnode = n_blocks - 1 + rb;  // heap index of the block's subtree node
@@ -69,7 +71,13 @@ __global__ __launch_bounds__(1024) void k_wsweep_prep(const SearchArgs a, uint16
                 out[e] = (__bf16)(-2.0f * df);
             }
             *reinterpret_cast<bf16x8_t *>(abf + int64_t(L) * NB * DP + (c * NB + i) * 8) = out;
-            n2 = reduce8(n2, OpAdd());  // the row's whole norm, in all 8 lanes
+            // the row's whole norm, in all of its lanes
+            if constexpr (CHUNKS == 8) {
+                n2 = reduce8(n2, OpAdd());
+            } else {
+                n2 += __shfl_xor(n2, 1);
+                n2 += __shfl_xor(n2, 2);
+            }
             if (c == 0) {
                 rn[int64_t(L) * NB + i] = vr ? n2 : kInf;
                 // non-negative floats order as unsigned integers
@@ -83,15 +91,18 @@ __global__ __launch_bounds__(1024) void k_wsweep_prep(const SearchArgs a, uint16
         // rounded up by 2^-12: far above the sum's rounding).  Then C_L - C_B.
         // The slot's first wave: lane = dimension, or lane = row for the
         // distances.
-        if (t < DP) {
+        if (t < 64) {
+            const bool dim = t < DP;
+            const int td = dim ? t : 0;
             const bool has = leaf_ok && cnt > 0;
             const float *bx = a.rbox + int64_t(node) * 2 * DP;
             const float *rows = a.rlpts + int64_t(leaf_ok ? L : 0) * a.r_leaf_slots * DP;
-            for (int r = 0; r < cnt; ++r) s_rows[ls][r][t] = rows[r * DP + t];
-            float cl = has ? 0.5f * (bx[t] + bx[DP + t]) : 0.f;
+            for (int r = 0; r < cnt; ++r)
+                if (dim) s_rows[ls][r][td] = rows[r * DP + td];
+            float cl = has ? 0.5f * (bx[td] + bx[DP + td]) : 0.f;
             float best_c = cl, best_r2 = kInf;
             for (int it = 0; it < kMebSteps && has; ++it) {
-                s_c[ls][t] = cl;
+                if (dim) s_c[ls][td] = cl;
                 asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
                 // lane r < cnt: squared distance of row r to the centre
                 float d2 = -1.0f;
@@ -116,12 +127,13 @@ __global__ __launch_bounds__(1024) void k_wsweep_prep(const SearchArgs a, uint16
                 }
                 const int f = __builtin_ctzll(ballot(d2 == m));
                 // (any centre is valid: the step needs no exact division)
-                cl += (s_rows[ls][f][t] - cl) * __builtin_amdgcn_rcpf(float(it + 2));
+                cl += (s_rows[ls][f][td] - cl) * __builtin_amdgcn_rcpf(float(it + 2));
                 asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
             }
-            const float df = has ? best_c - s_cb[t] : 0.f;
-            cbf[int64_t(rb) * NB * DP + ((t >> 3) * NB + l0 + ls) * 8 + (t & 7)] =
-                __builtin_bit_cast(uint16_t, (__bf16)(-2.0f * df));
+            const float df = has && dim ? best_c - s_cb[td] : 0.f;
+            if (dim)
+                cbf[int64_t(rb) * NB * DP + ((td >> 3) * NB + l0 + ls) * 8 + (td & 7)] =
+                    __builtin_bit_cast(uint16_t, (__bf16)(-2.0f * df));
             const float c2 = reduce64(df * df, OpAdd());
             if (t == 0) {
                 cn[L] = has ? c2 : kInf;
@@ -145,12 +157,18 @@ hipError_t launch_search_mfma_dp64(const SearchArgs &a, int K, int grid, hipStre
     return launch_search_mfma_sweep<64>(a, K, grid, s);
 }
 
-hipError_t launch_wsweep_prep(const SearchArgs &a, uint16_t *abf, float *rn, float *rlen, uint16_t *cbf,
-                              float *cn, float *lam, float *bcen, float *rcb, hipStream_t s) {
+hipError_t launch_wsweep_prep(const SearchArgs &a, int dp, uint16_t *abf, float *rn, float *rlen,
+                              uint16_t *cbf, float *cn, float *lam, float *bcen, float *rcb,
+                              hipStream_t s) {
     const int nl = a.r_first_leaf + 1;
     const int n_blocks = (nl + kSweepBlock - 1) / kSweepBlock;
     if (a.r_leaf_slots > 32) return hipErrorInvalidValue;
-    k_wsweep_prep<64><<<n_blocks, 1024, 0, s>>>(a, abf, rn, rlen, cbf, cn, lam, bcen, rcb);
+    if (dp == 64)
+        k_wsweep_prep<64><<<n_blocks, 1024, 0, s>>>(a, abf, rn, rlen, cbf, cn, lam, bcen, rcb);
+    else if (dp == 32)
+        k_wsweep_prep<32><<<n_blocks, 512, 0, s>>>(a, abf, rn, rlen, cbf, cn, lam, bcen, rcb);
+    else
+        return hipErrorInvalidValue;
     return hipGetLastError();
 }
 

@@ -1,4 +1,4 @@
-// High-dimensional k-NN (stride 64): a sweep over blocks of reference leaves
+// High-dimensional k-NN (stride 64, and FP32 requests at stride 32): a sweep over blocks of reference leaves
 // on the matrix unit, two query leaves per wavefront.  The traversal is the
 // pruning dual-tree traversal of Algorithm 1 in another order: every
 // (query node, reference leaf) pair is scored once and pruned when its
@@ -15,7 +15,9 @@
 // k = 50 search read 374 GB in 86.7 ms; with two leaves per wave each operand
 // read serves 64 queries, a lane holds its query's whole list (so its k-th
 // distance needs no merge of half-lists), and the operand layout makes every
-// load instruction one contiguous 1 KB.
+// load instruction one contiguous 1 KB.  At stride 32 the FP32 search of
+// 83,781 points by 34,155 queries (d = 32, k = 10) took 34.1 ms in the walk,
+// 2.0 ms here.
 //
 // Reference side (k_wsweep_prep, once per search): every row as BF16
 // -2 (r - C_B) centred on its block's centre C_B, the FP32 row norms, and
@@ -54,7 +56,10 @@ constexpr int kPairSortMax = 2048;
 template <int DP, int K>
 struct PairLds {
     static constexpr int row = DP + 4;  // floats per query row (padded: a lane per row)
-    static constexpr size_t q_rows = size_t(4) * 64 * row * 4;
+    // (at stride 32 the longest list of the parts form takes more)
+    static constexpr size_t four_waves = size_t(4) * 64 * row * 4;
+    static constexpr size_t one_list = size_t(64) * row * 4 + 64 * 4 + size_t(64) * K * 8;
+    static constexpr size_t q_rows = four_waves > one_list ? four_waves : one_list;
     // the block order and its keys; while they are sorted (in the query rows'
     // space) the centre sits in the keys' space
     static constexpr size_t off_okey = q_rows;
@@ -523,7 +528,9 @@ k_search_pair(const SearchArgs a) {
         }
         const int last = pad + a.k - 1;  // slot of the k-th entry
         if (a.walk_ties) {
-            // equal distances at the k-th place: in the order of the walk
+            // equal distances at the k-th place: in the order of the walk,
+            // whose slots hold one leaf at stride 64
+            const int ng_log2 = DP == 64 ? 0 : 6 - a.lpl_log2;
             float xk = 0.f, xn = 0.f;
 #pragma unroll
             for (int t = 0; t + 1 < K; ++t) {
@@ -545,7 +552,7 @@ k_search_pair(const SearchArgs a) {
                         if (d0 == xs && d1 == xs) {
                             const int i0 = uniform_i(__shfl(idx[t], src)),
                                       i1 = uniform_i(__shfl(idx[t + 1], src));
-                            if (walk_meets_second_first<DP>(a, i0, i1, ql, 0)) {
+                            if (walk_meets_second_first<DP>(a, i0, i1, ql, ng_log2)) {
                                 swapped = true;
                                 if (lane == src) {
                                     idx[t] = i1;

@@ -111,3 +111,17 @@ def test_walk_blocks_of_every_height(levels, d, leaf, k):
         few = knn.knn_search(rt, qt, k)
         torch.cuda.synchronize()
         assert torch.equal(walk[0], few[0]) and torch.equal(walk[1], few[1])
+
+
+# the same sweep at stride 32
+@pytest.mark.parametrize("n_ref,n_q,leaf", [(40, 5, 32), (1000, 1, 20), (1000, 700, 32),
+                                            (5000, 0, 16), (33_000, 900, 32), (3000, 20_000, 31)])
+@pytest.mark.parametrize("d,k,kind", [(17, 1, "random"), (20, 8, "twice"), (24, 16, "random"),
+                                      (32, 31, "twice"), (32, 10, "twice"), (30, 7, "random")])
+def test_fp32_sweep_at_stride_32(n_ref, n_q, leaf, d, k, kind):
+    test_fp32_sweep_equals_the_walk(n_ref, n_q, leaf, k, d, kind)
+
+
+@pytest.mark.parametrize("k", [6, 39, 51, 63])
+def test_fp32_sweep_at_stride_32_long_lists(k):
+    test_fp32_sweep_equals_the_walk(4000, 300, 32, k, 27, "random")
