@@ -219,8 +219,36 @@ knn_status search(const knn_tree *ref, const knn_tree *query, int k, const knn_o
     // and 0.36, 100,000 of 1M (d = 32) 217 and 14.3; of a 4-dimensional manifold
     // 200,000 of 500,000 (d = 24) 7.0 and 3.5; a mixture, 300,000 of 300,000
     // (d = 18, k = 3) 26.9 and 8.1.
-    const bool pair = (ref->dp == 64 || (ref->dp == 32 && !bf16)) && !arena && !dbg &&
-                      max_leaf <= 32 && ref->leaf_slots <= 32 && (bf16 || !opts.seed_radius);
+    bool pair = (ref->dp == 64 || (ref->dp == 32 && !bf16)) && !arena && !dbg &&
+                max_leaf <= 32 && ref->leaf_slots <= 32 && (bf16 || !opts.seed_radius);
+    Scratch sc{s, {}, arena};
+    uint16_t *abf = nullptr, *cbf = nullptr;
+    float *rn = nullptr, *rlen = nullptr, *cn = nullptr, *lam = nullptr, *bcen = nullptr, *rcb = nullptr;
+    if (pair) {
+        const int nl = int(ref->first_leaf) + 1;
+        const size_t pl = size_t((nl + kSweepBlock - 1) / kSweepBlock) * kSweepBlock;  // padded leaves
+        hipError_t e = hipSuccess;
+        auto take = [&](auto **out, size_t n) {
+            if (e == hipSuccess) e = sc.get(out, n);
+        };
+        take(&abf, pl * 32 * ref->dp);
+        take(&rn, pl * 32);
+        take(&rlen, pl);
+        take(&cbf, pl * ref->dp);
+        take(&cn, pl);
+        take(&lam, pl);
+        take(&bcen, pl / kSweepBlock * ref->dp);
+        take(&rcb, pl / kSweepBlock);
+        if (e == hipErrorOutOfMemory && !bf16) {
+            // no room for the operands: the walk needs none
+            (void)hipGetLastError();
+            dev_free_many(sc.p.data(), int(sc.p.size()), s);
+            sc.p.clear();
+            pair = false;
+        } else {
+            KNN_HIP(e);
+        }
+    }
     // what only a slot-per-wave walk can do: its counters describe whole query
     // leaves, and a leaf's second pass and largest k-th distance need the
     // leaf's queries in one wave
@@ -250,7 +278,6 @@ knn_status search(const knn_tree *ref, const knn_tree *query, int k, const knn_o
                             std::to_string(arena->bytes));
     }
 
-    Scratch sc{s, {}, arena};
     unsigned long long *dstats = nullptr;
     if (opts.stats) KNN_HIP(sc.get(&dstats, 2 * ST_COUNT));  // cleared before the launch
     int *fb_flag = nullptr, *fb_count = nullptr;
@@ -328,18 +355,6 @@ knn_status search(const knn_tree *ref, const knn_tree *query, int k, const knn_o
         KNN_HIP(zero_words(dstats, 2 * 2 * ST_COUNT, s));
     }
     if (pair) {  // the reference-side operands, made once per search
-        const int nl = int(ref->first_leaf) + 1;
-        const size_t pl = size_t((nl + kSweepBlock - 1) / kSweepBlock) * kSweepBlock;  // padded leaves
-        uint16_t *abf = nullptr, *cbf = nullptr;
-        float *rn = nullptr, *rlen = nullptr, *cn = nullptr, *lam = nullptr, *bcen = nullptr, *rcb = nullptr;
-        KNN_HIP(sc.get(&abf, pl * 32 * ref->dp));
-        KNN_HIP(sc.get(&rn, pl * 32));
-        KNN_HIP(sc.get(&rlen, pl));
-        KNN_HIP(sc.get(&cbf, pl * ref->dp));
-        KNN_HIP(sc.get(&cn, pl));
-        KNN_HIP(sc.get(&lam, pl));
-        KNN_HIP(sc.get(&bcen, pl / kSweepBlock * ref->dp));
-        KNN_HIP(sc.get(&rcb, pl / kSweepBlock));
         KNN_HIP(launch_wsweep_prep(a, ref->dp, abf, rn, rlen, cbf, cn, lam, bcen, rcb, s));
         a.sw_abf = abf;
         a.sw_rn = rn;

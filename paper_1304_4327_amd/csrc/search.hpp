@@ -55,7 +55,7 @@ struct SearchArgs {
     unsigned long long *stats;  // ST_COUNT counters, or NULL; the FP32 kernel with a
                                 // seed adds its second pass's counts to the next
                                 // ST_COUNT
-    // d = 64 sweep with two query leaves per wave (k_search_pair): the
+    // sweep with two query leaves per wave (k_search_pair): the
     // reference side of every tile and block Score, centred on the centre
     // C_B of the leaf's block (subtree of 32 leaves), made once per search
     // by k_wsweep_prep.  Leaves are padded to whole blocks.  An operand's 8
@@ -144,7 +144,7 @@ inline bool few_queries(int64_t n_q, int64_t n_ref, int d) {
 }
 hipError_t launch_search_few_d(const SearchArgs &a, int d, int64_t n_q, hipStream_t s);
 
-// the d = 64 sweep with two query leaves per wave (search_pair_d64.hip): the
+// the sweep with two query leaves per wave (search_pair_d32.hip, _d64.hip): the
 // operands of launch_wsweep_prep, lists of kk <= 64 entries
 constexpr int kPairLeaves = 8;  // query leaves per workgroup (two per wave)
 // parts: one pair of leaves per workgroup, its four waves dealing the blocks
@@ -160,7 +160,7 @@ hipError_t launch_search_pair_dp64(const SearchArgs &a, int kk, hipStream_t s);
 // reference leaves the d = 64 sweep scores together (one subtree)
 constexpr int kSweepBlock = 32;
 
-// reference-side operands of the wave-independent d = 64 sweep (see the
+// reference-side operands of the two-leaf sweep, strides 32 and 64 (see the
 // sw_* fields): fills them for the n_blocks * 32 (padded) leaves of the
 // reference tree in args
 hipError_t launch_wsweep_prep(const SearchArgs &args, int dp, uint16_t *abf, float *rn, float *rlen,
