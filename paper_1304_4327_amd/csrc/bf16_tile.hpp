@@ -54,6 +54,20 @@ __device__ __forceinline__ float bf16_margin_d8(float qlen, float rlen) {
     return C1 * qlen * rlen + C2 * (qlen + rlen) * (qlen + rlen);
 }
 
+// Lengths the bound above covers: centred norms from 2^-48, where the sums it
+// counts start to lose bits to numbers below FP32's smallest normal one (the
+// matrix unit takes those as 0), to 2^60, where norms and thresholds could
+// reach infinity.  A tile with |q'| + |r'| outside takes its candidates from
+// FP32 differences instead.
+constexpr float kTileShort = 0x1p-48f, kTileLong = 0x1p60f;
+
+// rows of a 32-row mask in the order of half h's tile values: bit r is row
+// 8 (r / 4) + 4 h + r % 4
+__device__ __forceinline__ uint32_t half_bits(uint32_t rows, int h) {
+    const uint32_t m = rows >> (4 * h);
+    return (m & 0xfu) | ((m >> 4) & 0xf0u) | ((m >> 8) & 0xf00u) | ((m >> 12) & 0xf000u);
+}
+
 // This lane's query operand: -2 (q - c) in BF16 over dimensions
 // 16 s + 8 h .. + 7 of each k-step s; returns the lane's part of |q - c|^2
 // (the two halves of a query sum to the whole).  qrow and cen are DP-strided

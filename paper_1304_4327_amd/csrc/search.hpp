@@ -61,13 +61,14 @@ struct SearchArgs {
     // by k_wsweep_prep.  Leaves are padded to whole blocks.  An operand's 8
     // dimensions 16 s + 8 h .. of 32 rows are 512 contiguous bytes.
     const uint16_t *sw_abf;  // [leaf][s][h][32 rows][8] bf16(-2 (r - C_B)), 0 past the leaf
-    const float *sw_rn;      // [leaf][32] |r - C_B|^2 (FP32), +inf past the leaf
+    const float *sw_rn;      // [leaf][32] |r - C_B|^2 (FP32, finite), +inf past the leaf
     const float *sw_rlen;    // [leaf] largest |r - C_B|, rounded up
     const uint16_t *sw_cbf;  // [block][s][h][32 leaves][8] bf16(-2 (C_L - C_B)), C_L the leaf's ball centre
-    const float *sw_cn;      // [leaf] |C_L - C_B|^2, +inf for empty or padding leaves
+    const float *sw_cn;      // [leaf] |C_L - C_B|^2 (finite), +inf for empty or padding leaves
     const float *sw_lam;     // [leaf] radius of the leaf's ball, 0 for padding
     const float *sw_bcen;    // [block][DP] C_B
-    const float *sw_rcb;     // [block] largest |C_L - C_B| of the block, rounded up
+    const float *sw_rcb;     // [block] largest |C_L - C_B| of the block, rounded up; +inf
+                             // where a norm of the block is beyond the tiles' range
     uint32_t *wave_log;         // debug: 8 words per wave (ticks, scores, tiles, inserts, passes, leaf,
                                 // staged tiles of the d = 64 sweep, candidates of the BF16 filters)
     // Score log of the debug kernel (launch_search_valu_debug_d3): one

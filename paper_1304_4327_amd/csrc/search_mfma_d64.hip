@@ -34,6 +34,7 @@ __global__ __launch_bounds__(16 * DP) void k_wsweep_prep(const SearchArgs a, uin
     __shared__ __align__(16) float s_c[4][DP];         // per leaf slot: the ball's centre
     __shared__ uint32_t s_rmax[4];  // per leaf slot: largest row norm (bits)
     __shared__ uint32_t s_max;      // the block: largest centre norm (bits)
+    __shared__ uint32_t s_row;      // the block: largest row norm (bits)
     const int rb = blockIdx.x;
     const int tid = threadIdx.x;
     const int ls = tid / TL, t = tid % TL;
@@ -48,7 +49,7 @@ __global__ __launch_bounds__(16 * DP) void k_wsweep_prep(const SearchArgs a, uin
         bcen[int64_t(rb) * DP + tid] = cc;
     }
     if (tid < 4) s_rmax[tid] = 0u;
-    if (tid == 0) s_max = 0u;
+    if (tid == 0) s_max = s_row = 0u;
     __syncthreads();
     for (int l0 = 0; l0 < NB; l0 += 4) {
         const int L = rb * NB + l0 + ls;
@@ -79,7 +80,8 @@ __global__ __launch_bounds__(16 * DP) void k_wsweep_prep(const SearchArgs a, uin
                 n2 += __shfl_xor(n2, 2);
             }
             if (c == 0) {
-                rn[int64_t(L) * NB + i] = vr ? n2 : kInf;
+                // (+inf is a row past the leaf; a row whose norm overflows is not)
+                rn[int64_t(L) * NB + i] = vr ? fminf(n2, 0x1.fffffep127f) : kInf;
                 // non-negative floats order as unsigned integers
                 if (vr) atomicMax(&s_rmax[ls], __float_as_uint(n2));
             }
@@ -121,6 +123,9 @@ __global__ __launch_bounds__(16 * DP) void k_wsweep_prep(const SearchArgs a, uin
                 }
                 const float m = __builtin_bit_cast(
                     float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, reduce64(d2, OpMax()))));
+                // (coordinates too far apart for FP32's range: the box centre,
+                // with an infinite radius)
+                if (!(m >= 0.f && m < kInf)) break;
                 if (m < best_r2) {
                     best_r2 = m;
                     best_c = cl;
@@ -136,19 +141,24 @@ __global__ __launch_bounds__(16 * DP) void k_wsweep_prep(const SearchArgs a, uin
                     __builtin_bit_cast(uint16_t, (__bf16)(-2.0f * df));
             const float c2 = reduce64(df * df, OpAdd());
             if (t == 0) {
-                cn[L] = has ? c2 : kInf;
+                cn[L] = has ? fminf(c2, 0x1.fffffep127f) : kInf;  // (NaN too: not empty)
                 lam[L] = has ? __builtin_amdgcn_sqrtf(best_r2) * (1.0f + 0x1p-12f) : 0.f;
                 if (has) atomicMax(&s_max, __float_as_uint(c2));
             }
         }
         __syncthreads();
         if (t == 0) {
+            atomicMax(&s_row, s_rmax[ls]);
             rlen[L] = __builtin_amdgcn_sqrtf(__uint_as_float(s_rmax[ls])) * (1.0f + 0x1p-20f);
             s_rmax[ls] = 0u;
         }
         __syncthreads();
     }
-    if (tid == 0) rcb[rb] = __builtin_amdgcn_sqrtf(__uint_as_float(s_max)) * (1.0f + 0x1p-20f);
+    // (+inf: some norm of the block is beyond the tiles' range)
+    if (tid == 0)
+        rcb[rb] = max(s_max, s_row) < __float_as_uint(0x1p116f)
+                      ? __builtin_amdgcn_sqrtf(__uint_as_float(s_max)) * (1.0f + 0x1p-20f)
+                      : kInf;
 }
 
 }  // namespace

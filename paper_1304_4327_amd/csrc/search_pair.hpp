@@ -33,6 +33,10 @@
 // margin of bf16_tile.hpp cannot beat the bound is skipped, every other one
 // gets its distance from the FP32 points in FP64, and only that value enters
 // a list or a bound.  So the search is exact for either precision request.
+// Where a block's norms or a query's distance to its centre lie outside the
+// range that the margin covers (coordinates some 1e17 apart and more, or all
+// within 1e-15), its leaves are scored by their boxes and its rows filtered by
+// FP32 differences, as in the walk.
 //
 // Lists.  K >= kk + 2 slots (kk = k, or k + 1 with the query's own point):
 // the k-th distance is slot K - 3, and the two extra entries hold what ties
@@ -175,7 +179,9 @@ k_search_pair(const SearchArgs a) {
             }
             sq = reduce8(sq, OpAdd());
             if (vb && (tid & 7) == 0) {
-                const float key = sqrtf(sq) * (1.0f - 0x1p-12f) - a.rlam[first + bi];
+                // (an overflow says nothing: such a block comes first)
+                const float key =
+                    sq < kInf ? sqrtf(sq) * (1.0f - 0x1p-12f) - a.rlam[first + bi] : -kInf;
                 s_sort[bi] = (uint64_t(f2key(key)) << 32) | uint32_t(bi);
             }
         }
@@ -259,7 +265,7 @@ k_search_pair(const SearchArgs a) {
     };
     // bounds after a change of the lists: B1, B2 over the leaf, B(Par) over
     // the pair; the parts exchange their k-th distances first
-    auto refresh = [&]() {
+    auto refresh = [&]() __attribute__((always_inline)) {
         float kth = dist[K - 3];
         if (parts) {
             const uint32_t mine = __float_as_uint(fmaxf(kth, 0.f));
@@ -283,28 +289,59 @@ k_search_pair(const SearchArgs a) {
     const __bf16 *abf = reinterpret_cast<const __bf16 *>(a.sw_abf);
     const __bf16 *cbf = reinterpret_cast<const __bf16 *>(a.sw_cbf);
 
-    for (int st = parts ? w : 0; st < n_steps && n_valid > 0; st += parts ? 4 : 1) {
+    // the rows of a leaf in `mask` (this half's 16 bits, then the other's),
+    // one per lane and round: the distance in FP64, then the list
+    auto insert_rows = [&](int leaf, int base, uint32_t mask) __attribute__((always_inline)) {
+        n_cand += __popc(mask);
+        const float *rows = a.rlpts + int64_t(leaf) * a.r_leaf_slots * DP;
+#pragma unroll 1
+        for (int pass = 0; pass < 32; ++pass) {
+            const bool has = mask != 0;
+            if (!ballot(has)) break;
+            ++n_pass;
+            const int b = has ? __builtin_ctz(mask) : 0;
+            mask &= mask - 1u;
+            const int rb16 = b & 15, hb = b < 16 ? hh : 1 - hh;
+            const int row = 8 * (rb16 >> 2) + 4 * hb + (rb16 & 3);
+            const float x0 = (float)d2_fp64_rows<DP>(my_q, rows + (has ? row : 0) * DP);
+            const float x = has ? x0 : kInf;
+            n_ins += (x < dist[K - 1]) ? 1u : 0u;
+            sorted_insert<K>(dist, idx, x, base + row);
+        }
+        refresh();
+    };
+    // whether the tiles' margin covers every query and row of a block
+    auto covered = [&](float qlen, float rcb) __attribute__((always_inline)) -> bool {
+        return rcb < 0.5f * kTileLong &&
+               !ballot(valid && !(qlen >= kTileShort && qlen < 0.5f * kTileLong));
+    };
+    // the block of a step (-1: none there, -2: no block from here on is needed)
+    auto block_of = [&](int st) __attribute__((always_inline)) -> int {
         int rb;
         if (use_sort) {
             rb = uniform_i(int(s_order[st]));
         } else {
             const int off = (st + 1) >> 1;
             rb = (st & 1) ? sblock + off : sblock - off;
-            if (rb < 0 || rb >= n_blocks) continue;  // uniform
+            if (rb < 0 || rb >= n_blocks) return -1;
         }
         if (parts) refresh();
         if (use_sort) {
             // no query of this wave needs a block whose key exceeds its bound
-            // plus R; the keys ascend
+            // plus R; the keys ascend (R and the keys are sums of squares: below
+            // 2^-40 they may have lost their bits)
             const float bw = uniform_f(reduce64(valid ? lim : -kInf, OpMax()));
             const float bmax =
                 bw < kInf ? __builtin_amdgcn_sqrtf(fmaxf(bw, 0.f)) * (1.0f + 0x1p-20f) : kInf;
-            if (uniform_f(s_okey[st]) > (bmax + R) * kSlack) break;
+            if (uniform_f(s_okey[st]) > fmaxf((bmax + R) * kSlack, 0x1p-40f)) return -2;
         }
-        // query operands of the block: q - C_B of column jj of both leaves at
-        // this lane's dimensions, and |q - C_B|^2 of this lane's query
+        return rb;
+    };
+    // query operands of a block: q - C_B of column jj of both leaves at this
+    // lane's dimensions; returns |q - C_B|^2 of this lane's query
+    auto operands = [&](int rb, bf16x8_t (&bq0)[S], bf16x8_t (&bq1)[S])
+                        __attribute__((always_inline)) -> float {
         const float *cb = a.sw_bcen + int64_t(rb) * DP;
-        bf16x8_t bq0[S], bq1[S];
         float n0 = 0.f, n1 = 0.f;
 #pragma unroll
         for (int s = 0; s < S; ++s) {
@@ -330,9 +367,23 @@ k_search_pair(const SearchArgs a) {
                 }
             }
         }
-        const float qnb = (hh ? n1 : n0) + __shfl_xor(hh ? n0 : n1, 32);
+        return (hh ? n1 : n0) + __shfl_xor(hh ? n0 : n1, 32);
+    };
+    bool left = false;  // blocks left for the pass below
+
+    for (int st = parts ? w : 0; st < n_steps && n_valid > 0; st += parts ? 4 : 1) {
+        const int rb = block_of(st);
+        if (rb == -2) break;
+        if (rb < 0) continue;
+        bf16x8_t bq0[S], bq1[S];
+        const float qnb = operands(rb, bq0, bq1);
         const float qlenb = sqrtf(qnb);
         const int L0 = rb * NB;
+        const float rcb = uniform_f(a.sw_rcb[rb]);
+        if (!covered(qlenb, rcb)) {
+            left = true;
+            continue;
+        }
         uint32_t own;  // the block's leaves that some query of the wave keeps
         {
             f32x16_t acc0, acc1;
@@ -359,7 +410,7 @@ k_search_pair(const SearchArgs a) {
                 acc1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ar, bq1[s], acc1, 0, 0, 0);
             }
             // idle lanes: a zero bound against a low end of +inf keeps nothing
-            const float low = valid ? qnb - bf16_margin<DP>(qlenb, uniform_f(a.sw_rcb[rb])) : kInf;
+            const float low = valid ? qnb - bf16_margin<DP>(qlenb, rcb) : kInf;
             const float bp = !valid      ? 0.f
                              : lim < kInf ? __builtin_amdgcn_sqrtf(fmaxf(lim, 0.f)) * (1.0f + 0x1p-20f)
                                           : kInf;
@@ -405,7 +456,7 @@ k_search_pair(const SearchArgs a) {
             t.rr = a.rrange[a.r_first_leaf + leaf];
             t.rl = a.sw_rlen[leaf];
         };
-        auto tile = [&](int leaf, const TileIn &t) {
+        auto tile = [&](int leaf, const TileIn &t) __attribute__((always_inline)) {
             const int base = uniform_i(t.rr.x);
             const int cnt = uniform_i(t.rr.y);
             ++n_tiles;
@@ -437,24 +488,8 @@ k_search_pair(const SearchArgs a) {
                 mk0 |= (__float_as_uint(acc0[r] - thr0) >> 31) << r;
                 mk1 |= (__float_as_uint(acc1[r] - thr1) >> 31) << r;
             }
-            uint32_t mask = (hh ? mk1 : mk0) | (uint32_t(__shfl_xor(int(hh ? mk0 : mk1), 32)) << 16);
-            n_cand += __popc(mask);
-            const float *rows = a.rlpts + int64_t(leaf) * a.r_leaf_slots * DP;
-#pragma unroll 1
-            for (int pass = 0; pass < 32; ++pass) {
-                const bool has = mask != 0;
-                if (!ballot(has)) break;
-                ++n_pass;
-                const int b = has ? __builtin_ctz(mask) : 0;
-                mask &= mask - 1u;
-                const int rb16 = b & 15, hb = b < 16 ? hh : 1 - hh;
-                const int row = 8 * (rb16 >> 2) + 4 * hb + (rb16 & 3);
-                const float x0 = (float)d2_fp64_rows<DP>(my_q, rows + (has ? row : 0) * DP);
-                const float x = has ? x0 : kInf;
-                n_ins += (x < dist[K - 1]) ? 1u : 0u;
-                sorted_insert<K>(dist, idx, x, base + row);
-            }
-            refresh();
+            insert_rows(leaf, base,
+                        (hh ? mk1 : mk0) | (uint32_t(__shfl_xor(int(hh ? mk0 : mk1), 32)) << 16));
             both(valid ? lim * kSlack - qnb : -kInf, base0, base1);
         };
         // software-pipelined over the kept leaves: the next one's operands
@@ -481,6 +516,49 @@ k_search_pair(const SearchArgs a) {
             tile(L0 + c1, t1);
             if (!m2) break;
             c0 = c2;
+        }
+    }
+
+    // the blocks that the margin does not cover: leaves scored by their boxes,
+    // rows filtered by FP32 differences
+    for (int st = parts ? w : 0; __builtin_expect(left, 0) && st < n_steps; st += parts ? 4 : 1) {
+        const int rb = block_of(st);
+        if (rb == -2) break;
+        if (rb < 0) continue;
+        bf16x8_t unused0[S], unused1[S];  // (the same sum as above: the same decision)
+        if (covered(sqrtf(operands(rb, unused0, unused1)), uniform_f(a.sw_rcb[rb]))) continue;
+        const int L0 = rb * NB;
+        uint32_t rest = uint32_t(ballot(lane < 32 && a.sw_cn[L0 + jj] < kInf));
+        n_score += __popc(rest);
+        for (; rest; rest &= rest - 1u) {
+            const int leaf = L0 + __builtin_ctz(rest);
+            const float *b = a.rbox + int64_t(a.r_first_leaf + leaf) * 2 * DP;
+            float sd = 0.f;
+#pragma unroll 4
+            for (int u = 0; u < DP; ++u) {
+                const float gap = fmaxf(fmaxf(b[u] - my_q[u], my_q[u] - b[DP + u]), 0.0f);
+                sd = fmaf(gap, gap, sd);
+            }
+            if (!ballot(valid && (a.bound == KNN_BOUND_NONE || !(sd > lim * kSlack)))) continue;
+            const int2 rr = a.rrange[a.r_first_leaf + leaf];
+            const int base = uniform_i(rr.x), cnt = uniform_i(rr.y);
+            ++n_tiles;
+            n_pairs += uint64_t(cnt) * uint64_t(n_valid);
+            const float *rows = a.rlpts + int64_t(leaf) * a.r_leaf_slots * DP;
+            const float thr = valid ? lim * kSlack * (1.0f + (DP + 6) * 0x1p-24f) : -1.0f;
+            uint32_t near = 0;
+#pragma unroll 1
+            for (int r = 0; r < cnt; ++r) {
+                float x = 0.f;
+#pragma unroll 4
+                for (int u = 0; u < DP; ++u) {
+                    const float df = my_q[u] - rows[r * DP + u];
+                    x = fmaf(df, df, x);
+                }
+                near |= uint32_t(x <= thr && x < kInf) << r;
+            }
+            if (ballot(near != 0))
+                insert_rows(leaf, base, half_bits(near, hh) | (half_bits(near, 1 - hh) << 16));
         }
     }
 
