@@ -234,6 +234,7 @@ __device__ __forceinline__ void search_valu_body(const SearchArgs &a) {
     [[maybe_unused]] bf16x8_t bq0[S], bq1[S];
     [[maybe_unused]] float qn_mt = 0.f, qlen_mt = 0.f;
     [[maybe_unused]] float qlen0 = 0.f, qlen1 = 0.f, base0 = 0.f, base1 = 0.f;
+    [[maybe_unused]] uint32_t rlen_from = 0, rlen_span = 0;
     // this lane's value and its partner's, as (leaf 0's query jj, leaf 1's)
     auto both = [&](float v, float &v0, float &v1) {
         const float o = __shfl_xor(v, 32);
@@ -275,6 +276,18 @@ __device__ __forceinline__ void search_valu_body(const SearchArgs &a) {
         }
         qlen_mt = sqrtf(qn_mt);
         both(qlen_mt, qlen0, qlen1);
+        // the tiles' margin covers a tile whose largest |r - c| lies between
+        // these two for every query of the wave (their bits as integers)
+        float qmin = valid ? qlen_mt : kInf, qmax = valid ? qlen_mt : 0.f;
+#pragma unroll
+        for (int l = 0; l < 6; ++l) {
+            qmin = xor_level(qmin, l, OpMin());
+            qmax = xor_level(qmax, l, OpMax());
+        }
+        const float from = uniform_f(fmaxf(kTileShort - qmin, 0.f));
+        const float to = uniform_f(fmaxf(kTileLong - qmax, 0.f));
+        rlen_from = __float_as_uint(from);
+        rlen_span = to > from ? __float_as_uint(to) - rlen_from : 0u;
     }
     const float lam2 = has_leaf ? 2.0f * a.qlam[qnode] : 0.f;
     // seeded form: a seed is only a pruning radius; NaN or negative values
@@ -478,6 +491,29 @@ __device__ __forceinline__ void search_valu_body(const SearchArgs &a) {
     // B bounds the point's final k-th distance, so anything farther cannot
     // enter its final list (equal distances aside).
     constexpr int CH = DP >= 32 ? 1 : 32 / DP;
+    // MT: the rows of a leaf whose FP32 distance passes the filter of the plain
+    // form, one bit each
+    auto near_rows = [&](const float *rp, int cnt) __attribute__((always_inline)) -> uint32_t {
+        const float lim = fminf(dist[K - 1], bound2 * kSlack);
+        const float thr = valid ? (RESCORE ? lim * kGamma : lim) : -kInf;
+        uint32_t rows = 0;
+#pragma unroll 1
+        for (int t0 = 0; t0 < cnt; t0 += CH) {  // (whole batches stay in the leaf's slots)
+            uint32_t bits = 0;
+#pragma unroll
+            for (int c = 0; c < CH; ++c) {
+                float sd = 0.f;
+#pragma unroll
+                for (int j = 0; j < D; ++j) {
+                    const float df = q[j] - rp[(t0 + c) * DP + j];
+                    sd = fmaf(df, df, sd);
+                }
+                bits |= uint32_t(sd < thr) << c;
+            }
+            rows |= bits << t0;
+        }
+        return cnt < 32 ? rows & ((1u << cnt) - 1u) : rows;
+    };
     auto tile = [&](int node) {
         ++n_tiles;
         const int2 rr = a.rrange[node];
@@ -517,6 +553,7 @@ __device__ __forceinline__ void search_valu_body(const SearchArgs &a) {
             if constexpr (D != 8) rn += __shfl_xor(rn, 32);  // the row's whole norm
             // largest |r - c| of the tile
             const float rlen = bf16_tile_rlen(rn, vr);
+            const uint64_t beyond = ballot(__float_as_uint(rlen) - rlen_from >= rlen_span);
             // thresholds of the two columns: base + margin (the margin is 1.25
             // times the proven bound, so the strict test keeps every row the
             // bound admits), capped at the largest BF16 number
@@ -538,24 +575,33 @@ __device__ __forceinline__ void search_valu_body(const SearchArgs &a) {
             uint32_t any = 0;
 #pragma unroll
             for (int r = 0; r < 16; ++r) any |= __float_as_uint(acc0[r]) | __float_as_uint(acc1[r]);
-            if (!ballot(int32_t(any) < 0)) return;  // lists unchanged, and so the bound
-            // bit r: the sign of value r; this lane keeps the rows of half hh
-            // for its own query and takes the other half's from lane ^ 32
-            uint32_t mk0 = 0, mk1 = 0;
-#pragma unroll
-            for (int r = 15; r >= 0; --r) {
-                mk0 = __builtin_amdgcn_alignbit(mk0, __float_as_uint(acc0[r]), 31);
-                mk1 = __builtin_amdgcn_alignbit(mk1, __float_as_uint(acc1[r]), 31);
-            }
-            const uint32_t own = hh ? mk1 : mk0;
-            const uint32_t oth = uint32_t(__shfl_xor(int(hh ? mk0 : mk1), 32));
+            if (!(ballot(int32_t(any) < 0) | beyond)) return;  // lists unchanged, and so the bound
             // FP32 requests take the rows in ascending order, as the plain
             // form does (it decides which of two equal distances is kept);
             // BF16 ones first the rows of their half
-            auto spread = [](uint32_t m, int h) {
-                return ((m & 0xfu) | ((m & 0xf0u) << 4) | ((m & 0xf00u) << 8) | ((m & 0xf000u) << 12)) << (4 * h);
-            };
-            uint32_t mask = a.walk_ties ? spread(own, hh) | spread(oth, 1 - hh) : own | (oth << 16);
+            uint32_t mask;
+            if (beyond) {
+                // out of the margin's range (coordinates some 1e18 apart, or
+                // all within 1e-15), whatever the products say: the FP32
+                // filter of the plain form
+                mask = near_rows(rp, cnt);
+                if (!a.walk_ties) mask = half_bits(mask, hh) | (half_bits(mask, 1 - hh) << 16);
+            } else {
+                // bit r: the sign of value r; this lane keeps the rows of half hh
+                // for its own query and takes the other half's from lane ^ 32
+                uint32_t mk0 = 0, mk1 = 0;
+#pragma unroll
+                for (int r = 15; r >= 0; --r) {
+                    mk0 = __builtin_amdgcn_alignbit(mk0, __float_as_uint(acc0[r]), 31);
+                    mk1 = __builtin_amdgcn_alignbit(mk1, __float_as_uint(acc1[r]), 31);
+                }
+                const uint32_t own = hh ? mk1 : mk0;
+                const uint32_t oth = uint32_t(__shfl_xor(int(hh ? mk0 : mk1), 32));
+                auto spread = [](uint32_t m, int h) {
+                    return ((m & 0xfu) | ((m & 0xf0u) << 4) | ((m & 0xf00u) << 8) | ((m & 0xf000u) << 12)) << (4 * h);
+                };
+                mask = a.walk_ties ? spread(own, hh) | spread(oth, 1 - hh) : own | (oth << 16);
+            }
             n_cand += __popc(mask);
             // survivors: one per lane per round, re-scored, inserted (a lane
             // without one re-scores row 0 and inserts +inf, a no-op)
