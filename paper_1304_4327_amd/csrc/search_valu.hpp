@@ -235,6 +235,7 @@ __device__ __forceinline__ void search_valu_body(const SearchArgs &a) {
     [[maybe_unused]] float qn_mt = 0.f, qlen_mt = 0.f;
     [[maybe_unused]] float qlen0 = 0.f, qlen1 = 0.f, base0 = 0.f, base1 = 0.f;
     [[maybe_unused]] uint32_t rlen_from = 0, rlen_span = 0;
+    [[maybe_unused]] int loose = 0;  // tiles in a row, nearly, whose products let too much through
     // this lane's value and its partner's, as (leaf 0's query jj, leaf 1's)
     auto both = [&](float v, float &v0, float &v1) {
         const float o = __shfl_xor(v, 32);
@@ -492,27 +493,37 @@ __device__ __forceinline__ void search_valu_body(const SearchArgs &a) {
     // enter its final list (equal distances aside).
     constexpr int CH = DP >= 32 ? 1 : 32 / DP;
     // MT: the rows of a leaf whose FP32 distance passes the filter of the plain
-    // form, one bit each
+    // form, one bit each.  A lane loads half a row and the rows are broadcast
+    // from the lanes: one wait a leaf, where row by row through the scalar cache
+    // a wave that has its SIMD to itself waits for each (200,000 by 200,000
+    // points of a crowded mixture, d = 16, k = 10: 25.2 ms so, 16.6 here)
     auto near_rows = [&](const float *rp, int cnt) __attribute__((always_inline)) -> uint32_t {
         const float lim = fminf(dist[K - 1], bound2 * kSlack);
         const float thr = valid ? (RESCORE ? lim * kGamma : lim) : -kInf;
         uint32_t rows = 0;
-#pragma unroll 1
-        for (int t0 = 0; t0 < cnt; t0 += CH) {  // (whole batches stay in the leaf's slots)
-            uint32_t bits = 0;
+        constexpr int H = D / 2;  // dimensions of a lane: row jj, half hh
+        float x[H];
+        {
+            const float *row = rp + (jj < cnt ? jj : 0) * DP + hh * H;
 #pragma unroll
-            for (int c = 0; c < CH; ++c) {
-                float sd = 0.f;
-#pragma unroll
-                for (int j = 0; j < D; ++j) {
-                    const float df = q[j] - rp[(t0 + c) * DP + j];
-                    sd = fmaf(df, df, sd);
-                }
-                bits |= uint32_t(sd < thr) << c;
+            for (int u = 0; u < H; u += 4) {
+                const float4 v = *reinterpret_cast<const float4 *>(row + u);
+                x[u] = v.x, x[u + 1] = v.y, x[u + 2] = v.z, x[u + 3] = v.w;
             }
-            rows |= bits << t0;
         }
-        return cnt < 32 ? rows & ((1u << cnt) - 1u) : rows;
+#pragma unroll 2
+        for (int t = 0; t < cnt; ++t) {  // (the same sums as the plain form's)
+            float sd = 0.f;
+#pragma unroll
+            for (int j = 0; j < D; ++j) {
+                const float r = __builtin_bit_cast(
+                    float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x[j % H]), t + 32 * (j / H)));
+                const float df = q[j] - r;
+                sd = fmaf(df, df, sd);
+            }
+            rows |= uint32_t(sd < thr) << t;
+        }
+        return rows;
     };
     auto tile = [&](int node) {
         ++n_tiles;
@@ -522,85 +533,109 @@ __device__ __forceinline__ void search_valu_body(const SearchArgs &a) {
         const float *rp = a.rlpts + int64_t(node - a.r_first_leaf) * a.r_leaf_slots * DP;
         n_pairs += uint64_t(cnt) * uint64_t(n_valid);
         if constexpr (MT) {
-            // reference operand: row jj, the dimensions of half hh, centred
-            // (d = 8: all dimensions, the high BF16 part in half 0, the low
-            // one in half 1)
-            const bool vr = jj < cnt;
-            const float *row = rp + (vr ? jj : 0) * DP + (D == 8 ? 0 : hh * 8);
-            bf16x8_t ar[S];
-            float rn = 0.f;
+            // the rows that may enter a list, one bit each, by the products or by
+            // the FP32 filter of the plain form: beyond the margin's range
+            // (coordinates some 1e18 apart, or all within 1e-15), on top of the
+            // products where these let too many rows through, and in their place
+            // once that is the rule in this wave.  Without the filter a wave
+            // whose leaves span the gap between two clusters re-scored nearly
+            // every row it met: 18,500 rounds against 1,300 in the plain form
+            // (150,000 references, 90,000 queries of a mixture, d = 13: 9.6 ms
+            // plain, 15.0 without the filter).  ms plain, without and with it,
+            // k = 10: 150,000 by 140,000 crowded points d = 13 13.6, 34.7 and
+            // 12.3; 40,000 by 90,000 d = 8 mixture 1.02, 1.41 and 0.94
+            uint32_t mask = ~0u;
+            bool fp32 = loose >= 8;
+            if (!fp32) {
+                // reference operand: row jj, the dimensions of half hh, centred
+                // (d = 8: all dimensions, the high BF16 part in half 0, the low
+                // one in half 1)
+                const bool vr = jj < cnt;
+                const float *row = rp + (vr ? jj : 0) * DP + (D == 8 ? 0 : hh * 8);
+                bf16x8_t ar[S];
+                float rn = 0.f;
 #pragma unroll
-            for (int s = 0; s < S; ++s) {
-                const float4 x0 = *reinterpret_cast<const float4 *>(row + s * 16);
-                const float4 x1 = *reinterpret_cast<const float4 *>(row + s * 16 + 4);
-                const float xv[8] = {x0.x, x0.y, x0.z, x0.w, x1.x, x1.y, x1.z, x1.w};
+                for (int s = 0; s < S; ++s) {
+                    const float4 x0 = *reinterpret_cast<const float4 *>(row + s * 16);
+                    const float4 x1 = *reinterpret_cast<const float4 *>(row + s * 16 + 4);
+                    const float xv[8] = {x0.x, x0.y, x0.z, x0.w, x1.x, x1.y, x1.z, x1.w};
 #pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    // (a row past the leaf repeats row 0: its start value is
-                    // +inf, and a select here made the compiler load the row
-                    // in two dependent steps)
-                    const float rd = xv[e] - tcen[s * 8 + e];
-                    rn = fmaf(rd, rd, rn);
-                    if constexpr (D == 8) {
-                        const __bf16 h = (__bf16)rd;
-                        const __bf16 l = (__bf16)(rd - float(h));
-                        ar[0][e] = hh ? l : h;
-                    } else {
-                        ar[s][e] = (__bf16)rd;
+                    for (int e = 0; e < 8; ++e) {
+                        // (a row past the leaf repeats row 0: its start value is
+                        // +inf, and a select here made the compiler load the row
+                        // in two dependent steps)
+                        const float rd = xv[e] - tcen[s * 8 + e];
+                        rn = fmaf(rd, rd, rn);
+                        if constexpr (D == 8) {
+                            const __bf16 h = (__bf16)rd;
+                            const __bf16 l = (__bf16)(rd - float(h));
+                            ar[0][e] = hh ? l : h;
+                        } else {
+                            ar[s][e] = (__bf16)rd;
+                        }
                     }
                 }
-            }
-            if constexpr (D != 8) rn += __shfl_xor(rn, 32);  // the row's whole norm
-            // largest |r - c| of the tile
-            const float rlen = bf16_tile_rlen(rn, vr);
-            const uint64_t beyond = ballot(__float_as_uint(rlen) - rlen_from >= rlen_span);
-            // thresholds of the two columns: base + margin (the margin is 1.25
-            // times the proven bound, so the strict test keeps every row the
-            // bound admits), capped at the largest BF16 number
-            auto margin = [&](float ql) {
-                return D == 8 ? bf16_margin_d8(ql, rlen) : bf16_margin<DP>(ql, rlen);
-            };
-            const float thr0 = fminf(base0 + margin(qlen0), 0x1.fep127f);
-            const float thr1 = fminf(base1 + margin(qlen1), 0x1.fep127f);
-            // the accumulators start at |r - c|^2 - threshold, from one more
-            // product each: a value's sign says whether the row is a candidate
-            f32x16_t acc0 = bf16_start(rn, vr, thr0, valid_0, hh);
-            f32x16_t acc1 = bf16_start(rn, vr, thr1, valid_1, hh);
-#pragma unroll
-            for (int s = 0; s < S; ++s) {
-                acc0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ar[s], bq0[s], acc0, 0, 0, 0);
-                acc1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ar[s], bq1[s], acc1, 0, 0, 0);
-            }
-            // most tiles hold no candidate: one OR of all signs
-            uint32_t any = 0;
-#pragma unroll
-            for (int r = 0; r < 16; ++r) any |= __float_as_uint(acc0[r]) | __float_as_uint(acc1[r]);
-            if (!(ballot(int32_t(any) < 0) | beyond)) return;  // lists unchanged, and so the bound
-            // FP32 requests take the rows in ascending order, as the plain
-            // form does (it decides which of two equal distances is kept);
-            // BF16 ones first the rows of their half
-            uint32_t mask;
-            if (beyond) {
-                // out of the margin's range (coordinates some 1e18 apart, or
-                // all within 1e-15), whatever the products say: the FP32
-                // filter of the plain form
-                mask = near_rows(rp, cnt);
-                if (!a.walk_ties) mask = half_bits(mask, hh) | (half_bits(mask, 1 - hh) << 16);
-            } else {
-                // bit r: the sign of value r; this lane keeps the rows of half hh
-                // for its own query and takes the other half's from lane ^ 32
-                uint32_t mk0 = 0, mk1 = 0;
-#pragma unroll
-                for (int r = 15; r >= 0; --r) {
-                    mk0 = __builtin_amdgcn_alignbit(mk0, __float_as_uint(acc0[r]), 31);
-                    mk1 = __builtin_amdgcn_alignbit(mk1, __float_as_uint(acc1[r]), 31);
-                }
-                const uint32_t own = hh ? mk1 : mk0;
-                const uint32_t oth = uint32_t(__shfl_xor(int(hh ? mk0 : mk1), 32));
-                auto spread = [](uint32_t m, int h) {
-                    return ((m & 0xfu) | ((m & 0xf0u) << 4) | ((m & 0xf00u) << 8) | ((m & 0xf000u) << 12)) << (4 * h);
+                if constexpr (D != 8) rn += __shfl_xor(rn, 32);  // the row's whole norm
+                // largest |r - c| of the tile
+                const float rlen = bf16_tile_rlen(rn, vr);
+                const uint64_t beyond = ballot(__float_as_uint(rlen) - rlen_from >= rlen_span);
+                // thresholds of the two columns: base + margin (the margin is 1.25
+                // times the proven bound, so the strict test keeps every row the
+                // bound admits), capped at the largest BF16 number
+                auto margin = [&](float ql) {
+                    return D == 8 ? bf16_margin_d8(ql, rlen) : bf16_margin<DP>(ql, rlen);
                 };
-                mask = a.walk_ties ? spread(own, hh) | spread(oth, 1 - hh) : own | (oth << 16);
+                const float thr0 = fminf(base0 + margin(qlen0), 0x1.fep127f);
+                const float thr1 = fminf(base1 + margin(qlen1), 0x1.fep127f);
+                // the accumulators start at |r - c|^2 - threshold, from one more
+                // product each: a value's sign says whether the row is a candidate
+                f32x16_t acc0 = bf16_start(rn, vr, thr0, valid_0, hh);
+                f32x16_t acc1 = bf16_start(rn, vr, thr1, valid_1, hh);
+#pragma unroll
+                for (int s = 0; s < S; ++s) {
+                    acc0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ar[s], bq0[s], acc0, 0, 0, 0);
+                    acc1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ar[s], bq1[s], acc1, 0, 0, 0);
+                }
+                // most tiles hold no candidate: one OR of all signs
+                uint32_t any = 0;
+#pragma unroll
+                for (int r = 0; r < 16; ++r) any |= __float_as_uint(acc0[r]) | __float_as_uint(acc1[r]);
+                if (!(ballot(int32_t(any) < 0) | beyond)) {
+                    loose = max(loose - 4, 0);
+                    return;  // lists unchanged, and so the bound
+                }
+                fp32 = beyond != 0;
+                if (!fp32) {
+                    // bit r: the sign of value r; this lane keeps the rows of half hh
+                    // for its own query and takes the other half's from lane ^ 32
+                    uint32_t mk0 = 0, mk1 = 0;
+#pragma unroll
+                    for (int r = 15; r >= 0; --r) {
+                        mk0 = __builtin_amdgcn_alignbit(mk0, __float_as_uint(acc0[r]), 31);
+                        mk1 = __builtin_amdgcn_alignbit(mk1, __float_as_uint(acc1[r]), 31);
+                    }
+                    const uint32_t own = hh ? mk1 : mk0;
+                    const uint32_t oth = uint32_t(__shfl_xor(int(hh ? mk0 : mk1), 32));
+                    // FP32 requests take the rows in ascending order, as the plain
+                    // form does (it decides which of two equal distances is kept);
+                    // BF16 ones first the rows of their half
+                    auto spread = [](uint32_t m, int h) {
+                        return ((m & 0xfu) | ((m & 0xf0u) << 4) | ((m & 0xf00u) << 8) | ((m & 0xf000u) << 12)) << (4 * h);
+                    };
+                    mask = a.walk_ties ? spread(own, hh) | spread(oth, 1 - hh) : own | (oth << 16);
+                    // whether the margin is what lets rows through: leaves that span
+                    // the gap between two clusters lie far from their centre, and
+                    // all of a tile's rows may pass for them (one round each below;
+                    // the FP32 filter costs as much as eight)
+                    fp32 = ballot(__popc(mask) > 10 &&
+                                  margin(hh ? qlen1 : qlen0) > 0.25f * fminf(dist[K - 1], bound2)) != 0;
+                    loose = fp32 ? loose + 1 : max(loose - 4, 0);
+                }
+            }
+            if (fp32) {
+                const uint32_t rows = near_rows(rp, cnt);
+                if (!ballot(rows != 0)) return;
+                mask &= a.walk_ties ? rows : half_bits(rows, hh) | (half_bits(rows, 1 - hh) << 16);
             }
             n_cand += __popc(mask);
             // survivors: one per lane per round, re-scored, inserted (a lane
