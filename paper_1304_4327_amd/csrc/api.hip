@@ -197,9 +197,15 @@ knn_status search(const knn_tree *ref, const knn_tree *query, int k, const knn_o
     // two leaves a wave too (the visit order depends on the slot); it returns
     // what that form returns: 2M queries of 2M points at d = 8, k = 10 67 ms
     // plain, 50 here; 150,000 points on themselves at d = 13, k = 7 1.72 ms
-    // plain, 1.21 here.  The seeded form stays plain.
+    // plain, 1.21 here.  The seeded form stays plain, and so do small reference
+    // sets, whose walks are over before the lists have filled and a tile's
+    // products can drop much: plain / here, us, 140,000 queries, k = 10, d = 9, of
+    // a crowded mixture 1000 references 271 / 350, 10,000 1097 / 1202, 40,000 3.50
+    // and 2.89 ms; uniform 1000 443 / 326, 10,000 3.06 and 1.62 ms; 200,000
+    // queries, d = 13, of 4000 points of a mixture 420 / 500, of a manifold 443 /
+    // 333.
     const bool mt32 = !bf16 && !dbg && !opts.seed_radius && (ref->dp == 8 || ref->dp == 16) &&
-                      lpl_log2 == 5 && ref->leaf_slots <= 32 && K <= 16;
+                      lpl_log2 == 5 && ref->leaf_slots <= 32 && K <= 16 && ref->n >= kTilePoints;
     const int NG = 64 >> lpl_log2;
     const int nq_leaves = int(qt->n_leaves);
     if (dbg && (ref->d != 3 || bf16 || opts.seed_radius || K > 16))

@@ -124,6 +124,8 @@ hipError_t launch_search_valu_debug_d3(const SearchArgs &a, int K, int grid, hip
 // (lpl_log2 = 5), reference leaves of <= 32 points, K <= 16; the seeded form
 // when a.seed is set
 // (stride 8 in the plain form only)
+// references from which FP32 requests use them
+constexpr int64_t kTilePoints = 4096;
 hipError_t launch_search_mt_d8(const SearchArgs &a, int K, int grid, hipStream_t s);
 hipError_t launch_search_mt_d16(const SearchArgs &a, int K, int grid, hipStream_t s);
 hipError_t launch_search_mt_d32(const SearchArgs &a, int K, int grid, hipStream_t s);

@@ -543,7 +543,7 @@ __device__ __forceinline__ void search_valu_body(const SearchArgs &a) {
             // (150,000 references, 90,000 queries of a mixture, d = 13: 9.6 ms
             // plain, 15.0 without the filter).  ms plain, without and with it,
             // k = 10: 150,000 by 140,000 crowded points d = 13 13.6, 34.7 and
-            // 12.3; 40,000 by 90,000 d = 8 mixture 1.02, 1.41 and 0.94
+            // 12.0; 40,000 by 90,000 d = 8 mixture 1.01, 1.43 and 0.99
             uint32_t mask = ~0u;
             bool fp32 = loose >= 8;
             if (!fp32) {
