@@ -259,9 +259,10 @@ knn_status search(const knn_tree *ref, const knn_tree *query, int k, const knn_o
     // leaves, and a leaf's second pass and largest k-th distance need the
     // leaf's queries in one wave
     const bool whole = dbg || opts.stats || opts.seed_radius || opts.leaf_kth_out || wlog_path;
+    const int kk = k + (opts.exclude_self ? 1 : 0);  // list entries wanted
     const bool few = !pair && ref->dp <= 16 && (!bf16 || mt) && !whole &&
-                     opts.bound != KNN_BOUND_NONE && k + (opts.exclude_self ? 1 : 0) <= kFewList &&
-                     few_queries(qt->n, ref->n, ref->d);
+                     opts.bound != KNN_BOUND_NONE && kk <= kFewList &&
+                     few_queries(qt->n, ref->n, ref->d, kk);
     // few slots: several waves share one.  The pair sweep: the four waves of a
     // workgroup take one pair of leaves while that leaves CUs idle otherwise
     const int split = pair ? (pair_parts(nq_leaves) ? 1 : 0)
@@ -386,7 +387,6 @@ knn_status search(const knn_tree *ref, const knn_tree *query, int k, const knn_o
         KNN_HIP(hipEventRecord(ev[0], s));
     }
     auto launch_pair = [&](const SearchArgs &x) {
-        const int kk = k + (opts.exclude_self ? 1 : 0);
         return ref->dp == 64 ? launch_search_pair_dp64(x, kk, s) : launch_search_pair_dp32(x, kk, s);
     };
     KNN_HIP(dbg    ? launch_search_valu_debug_d3(a, K, grid, s)

@@ -3,6 +3,8 @@
 
 #include "common.hpp"
 
+#include <algorithm>
+
 namespace knnx {
 
 // counters accumulated by the traversal kernels (uint64 each)
@@ -134,16 +136,33 @@ hipError_t launch_search_mt_d32(const SearchArgs &a, int K, int grid, hipStream_
 // but KNN_BOUND_NONE, no seed, no counters; lists of kk <= kFewList entries.
 // The slot-per-wave walk lasts as long as its slowest wave until the chip is
 // full, and a slot's queries open the more of the reference tree the sparser
-// they lie in it; one query per wave costs the same per query throughout.
-// Measured (us, walk against one query per wave; k = 10, mixtures, d = 3):
-//   64,000 queries: 225 / 116 of 10,000 points, 798 / 132 of 200,000
-//   256,000 queries: 266 / 370 of 10,000, 565 / 419 of 200,000, 959 / 443 of 1.5M
-// and d = 8: 64,000 of 10,000 555 / 201, 256,000 of 200,000 3453 / 1987.
-// Above d = 8 its tiles re-score in FP64 and the walk has matrix-core tiles:
-// 1M of 4M at d = 16 takes 10.8 ms there, 13.1 ms here.
+// they lie in it; one query per wave costs the same per query throughout, about
+// 1.6 us a thousand at d = 3, 2 to 4 at d = 5, 6 to 15 at d = 8.
+// Measured (us, one query per wave / slot walk; k = 10, 32 points a leaf):
+//   mixtures, d = 3: 128,000 queries of 10,000 points 207 / 182, 256,000 of
+//   200,000 453 / 447, 512,000 of 1M 814 / 1031; d = 8: 128,000 of 10,000
+//   773 / 655, 256,000 of 200,000 3885 / 6400; d = 13: 66,000 of 10,000 and of
+//   40,000 372 / 1332 and 714 / 3315; a manifold, d = 13: 128,000 of 10,000
+//   605 / 412, of 200,000 1002 / 1314
+//   uniform, d = 2: 64,000 of 10,000 107 / 82, of 200,000 104 / 202; d = 3:
+//   64,000 of 10,000 116 / 137, 256,000 of 200,000 439 / 313; d = 13: 32,000 of
+//   10,000 1591 / 1450, 64,000 of 10,000 2960 / 1495, of 200,000 13.5 / 14.7 ms
+//   d = 1: 40,000 of 3000 66 / 52, of 150,000 73 / 114
+//   any d: 40,000 of 100 50 to 100 / 40 to 85, of 1000 52 to 90 / 50 to 210
+// So the line lies lower where every kind of data crosses early (d = 1, d = 2,
+// few references) and up to d = 8 inside what uniform sets bear; above d = 8,
+// where uniform sets cross at 30,000 to 70,000 queries and clustered ones gain
+// three times as much as those lose, between the two.  Lists of more than 16
+// entries cost the slot walk several times as much (40,000 queries of 1000, d =
+// 3, k = 40: 111 / 609), whatever the rest.
 constexpr int kFewList = 62;
-inline bool few_queries(int64_t n_q, int64_t n_ref, int d) {
-    return n_q <= 65536 + n_ref / (d <= 4 ? 6 : d <= 8 ? 2 : 8);
+inline bool few_queries(int64_t n_q, int64_t n_ref, int d, int kk) {
+    const int64_t most = 65536 + n_ref / (d <= 4 ? 6 : d <= 8 ? 2 : 8);
+    if (kk > 16) return n_q <= most;
+    const int64_t line = d == 1   ? 24576 + n_ref / 8
+                         : d == 2 ? std::min(most, 32768 + n_ref / 2)
+                                  : most;
+    return n_q <= std::min(line, 16384 + 48 * n_ref);
 }
 hipError_t launch_search_few_d(const SearchArgs &a, int d, int64_t n_q, hipStream_t s);
 

@@ -38,3 +38,19 @@ def _check(n_ref, n_q, d, k, leaf=32):
 @pytest.mark.parametrize("d", [5, 8, 9, 16])
 def test_tiles_by_references(n_ref, n_q, d):
     _check(n_ref, n_q, d, 10)
+
+
+# one query per wave: the last number of queries it takes and the next
+def _most(n_ref, d, k):
+    most = 65536 + n_ref // (6 if d <= 4 else 2 if d <= 8 else 8)
+    if k > 16:
+        return most
+    line = {1: 24576 + n_ref // 8, 2: min(most, 32768 + n_ref // 2)}.get(d, most)
+    return min(line, 16384 + 48 * n_ref)
+
+
+@pytest.mark.parametrize("n_ref", [100, 3000, 20_000])
+@pytest.mark.parametrize("d,k", [(1, 6), (2, 6), (2, 17), (3, 6), (8, 6), (12, 16)])
+def test_one_query_per_wave_by_queries(n_ref, d, k):
+    for more in (0, 1):
+        _check(n_ref, _most(n_ref, d, k) + more, d, k)
