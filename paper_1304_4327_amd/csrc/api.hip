@@ -202,8 +202,8 @@ knn_status search(const knn_tree *ref, const knn_tree *query, int k, const knn_o
     // products can drop much: plain / here, us, 140,000 queries, k = 10, d = 9, of
     // a crowded mixture 1000 references 271 / 350, 10,000 1097 / 1202, 40,000 3.50
     // and 2.89 ms; uniform 1000 443 / 326, 10,000 3.06 and 1.62 ms; 200,000
-    // queries, d = 13, of 4000 points of a mixture 420 / 500, of a manifold 443 /
-    // 333.
+    // queries, d = 13, of 2000 points of a mixture 305 / 356, of a manifold 337 /
+    // 285, uniform 808 / 546.
     const bool mt32 = !bf16 && !dbg && !opts.seed_radius && (ref->dp == 8 || ref->dp == 16) &&
                       lpl_log2 == 5 && ref->leaf_slots <= 32 && K <= 16 && ref->n >= kTilePoints;
     const int NG = 64 >> lpl_log2;

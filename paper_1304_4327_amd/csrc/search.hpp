@@ -127,7 +127,7 @@ hipError_t launch_search_valu_debug_d3(const SearchArgs &a, int K, int grid, hip
 // when a.seed is set
 // (stride 8 in the plain form only)
 // references from which FP32 requests use them
-constexpr int64_t kTilePoints = 4096;
+constexpr int64_t kTilePoints = 2048;
 hipError_t launch_search_mt_d8(const SearchArgs &a, int K, int grid, hipStream_t s);
 hipError_t launch_search_mt_d16(const SearchArgs &a, int K, int grid, hipStream_t s);
 hipError_t launch_search_mt_d32(const SearchArgs &a, int K, int grid, hipStream_t s);
@@ -142,7 +142,7 @@ hipError_t launch_search_mt_d32(const SearchArgs &a, int K, int grid, hipStream_
 //   mixtures, d = 3: 128,000 queries of 10,000 points 207 / 182, 256,000 of
 //   200,000 453 / 447, 512,000 of 1M 814 / 1031; d = 8: 128,000 of 10,000
 //   773 / 655, 256,000 of 200,000 3885 / 6400; d = 13: 66,000 of 10,000 and of
-//   40,000 372 / 1332 and 714 / 3315; a manifold, d = 13: 128,000 of 10,000
+//   40,000 343 / 1332 and 714 / 3315; a manifold, d = 13: 128,000 of 10,000
 //   605 / 412, of 200,000 1002 / 1314
 //   uniform, d = 2: 64,000 of 10,000 107 / 82, of 200,000 104 / 202; d = 3:
 //   64,000 of 10,000 116 / 137, 256,000 of 200,000 439 / 313; d = 13: 32,000 of

@@ -33,7 +33,7 @@ def _check(n_ref, n_q, d, k, leaf=32):
 
 
 # matrix-core tiles for FP32 requests
-@pytest.mark.parametrize("n_ref", [4095, 4096])
+@pytest.mark.parametrize("n_ref", [2047, 2048])
 @pytest.mark.parametrize("n_q", [500, 71_000])
 @pytest.mark.parametrize("d", [5, 8, 9, 16])
 def test_tiles_by_references(n_ref, n_q, d):
