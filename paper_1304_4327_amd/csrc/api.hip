@@ -225,8 +225,17 @@ knn_status search(const knn_tree *ref, const knn_tree *query, int k, const knn_o
     // and 0.36, 100,000 of 1M (d = 32) 217 and 14.3; of a 4-dimensional manifold
     // 200,000 of 500,000 (d = 24) 7.0 and 3.5; a mixture, 300,000 of 300,000
     // (d = 18, k = 3) 26.9 and 8.1.
+    // The operands cost a small call more than the sweep saves: FP32 requests
+    // take it from kSweepPoints references on (us with the walk and with the
+    // sweep, d = 32, k = 10, 500 queries: of a mixture, 1000 references 375 and
+    // 588, 2000 604 and 686, 4000 1010 and 695; of a manifold 393 and 587, 594
+    // and 613, 952 and 651; uniform 533 and 377, 864 and 373, 1590 and 369; with
+    // k = 1 the clustered sets cross near 3000).  The number of queries moves no
+    // line: one query of 10,000 clustered or manifold points takes 80 to 190 us in
+    // the walk and 230 to 330 in the sweep, one of uniform points 3.2 and 0.3 ms.
     bool pair = (ref->dp == 64 || (ref->dp == 32 && !bf16)) && !arena && !dbg &&
-                max_leaf <= 32 && ref->leaf_slots <= 32 && (bf16 || !opts.seed_radius);
+                max_leaf <= 32 && ref->leaf_slots <= 32 &&
+                (bf16 || (!opts.seed_radius && ref->n >= kSweepPoints));
     Scratch sc{s, {}, arena};
     uint16_t *abf = nullptr, *cbf = nullptr;
     float *rn = nullptr, *rlen = nullptr, *cn = nullptr, *lam = nullptr, *bcen = nullptr, *rcb = nullptr;

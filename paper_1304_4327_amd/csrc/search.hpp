@@ -168,6 +168,8 @@ hipError_t launch_search_few_d(const SearchArgs &a, int d, int64_t n_q, hipStrea
 
 // the sweep with two query leaves per wave (search_pair_d32.hip, _d64.hip): the
 // operands of launch_wsweep_prep, lists of kk <= 64 entries
+// references from which FP32 requests use it
+constexpr int64_t kSweepPoints = 3000;
 constexpr int kPairLeaves = 8;  // query leaves per workgroup (two per wave)
 // parts: one pair of leaves per workgroup, its four waves dealing the blocks
 inline int pair_grid(int n_leaves, bool parts) {

@@ -54,3 +54,12 @@ def _most(n_ref, d, k):
 def test_one_query_per_wave_by_queries(n_ref, d, k):
     for more in (0, 1):
         _check(n_ref, _most(n_ref, d, k) + more, d, k)
+
+
+# the sweep for FP32 requests
+@pytest.mark.parametrize("n_ref", [2999, 3000])
+@pytest.mark.parametrize("n_q", [1, 500, 20_000])
+@pytest.mark.parametrize("d", [17, 32, 33, 64])
+def test_sweep_by_references(n_ref, n_q, d):
+    for k in (10, 50):
+        _check(n_ref, n_q, d, k)
