@@ -691,14 +691,13 @@ k_search_pair(const SearchArgs a) {
             }
         }
     }
-    if (!writer) return;  // no barrier follows
     bool fb = false;
-    if (a.seed && valid) fb = !((double)worst * worst <= (double)seed2 * (1.0 - 0x1p-20));
+    if (writer && a.seed && valid) fb = !((double)worst * worst <= (double)seed2 * (1.0 - 0x1p-20));
     const float lw = reduce32(worst, OpMax());
     const float fl = reduce32(fb ? 1.0f : 0.0f, OpMax());
     const float fbb = reduce32((valid && worst < kInf) ? worst : kInf, OpMin());
     const uint64_t fbmask = ballot(fb);
-    if (jj == 0 && has_leaf) {
+    if (writer && jj == 0 && has_leaf) {
         if (a.leaf_kth) a.leaf_kth[qleaf] = fmaxf(lw, 0.0f);
         if (a.fallback && fl > 0.f) {
             a.fallback[qleaf] = 1;

@@ -1,0 +1,33 @@
+"""Counters of the sweep (stride 64, and FP32 at stride 32): every wave's work is
+counted, also where the four waves of a workgroup share a pair of query leaves."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+def _trees(ref, q, leaf=32):
+    import torch
+    from paper_1304_4327_amd import knn
+    return (knn.knn_build_tree(torch.from_numpy(ref).cuda(), leaf),
+            knn.knn_build_tree(torch.from_numpy(q).cuda(), leaf))
+
+
+# without pruning every pair of points is evaluated: one and two query leaves
+# spread over all references, whose blocks are dealt to four waves
+@pytest.mark.parametrize("d,precision", [(17, "fp32"), (32, "fp32"), (40, "fp32"), (64, "fp32"),
+                                         (64, "bf16")])
+@pytest.mark.parametrize("n_q", [32, 60])
+def test_every_pair_is_counted(d, precision, n_q):
+    from paper_1304_4327_amd import knn
+    print(f"counters d={d} {precision} n_q={n_q}", flush=True)
+    rng = np.random.default_rng(d)
+    ref = rng.random((5000, d)).astype(np.float32)
+    q = rng.random((n_q, d)).astype(np.float32)
+    rt, qt = _trees(ref, q)
+    _, _, st = knn.knn_search(rt, qt, 10, bound="none", precision=precision, stats=True)
+    assert st["pairs"] == n_q * 5000
+    leaves = knn.knn_tree_get_info(rt)["n_leaves"]
+    waves = -(-knn.knn_tree_get_info(qt)["n_leaves"] // 2)
+    assert st["leaf_tiles"] == st["score_calls"] == waves * leaves
+    assert st["inserts"] >= n_q * 10
