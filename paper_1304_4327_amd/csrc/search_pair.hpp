@@ -326,7 +326,7 @@ k_search_pair(const SearchArgs a) {
             if (rb < 0 || rb >= n_blocks) return -1;
         }
         if (parts) refresh();
-        if (use_sort) {
+        if (use_sort && a.bound != KNN_BOUND_NONE) {
             // no query of this wave needs a block whose key exceeds its bound
             // plus R; the keys ascend (R and the keys are sums of squares: below
             // 2^-40 they may have lost their bits)
