@@ -35,6 +35,7 @@
 #include <thread>
 
 #include <algorithm>
+#include <atomic>
 #include <type_traits>
 #include <vector>
 
@@ -693,6 +694,7 @@ constexpr int kSegLds = 159 * 1024;
 constexpr int kSmallSeg = 1024;  // points of a segment that four waves finish
 template <int DP, int NW>
 struct SegCfg {
+    static constexpr int waves = NW;
     static constexpr bool staged = DP <= 16;  // points in LDS
     // 16 rows of a leaf at a time per wave, for the long rows
     static constexpr int tile_rows = 16, tile_row = DP + 1;
@@ -1386,6 +1388,24 @@ __global__ __launch_bounds__(1024) void k_lambda_top(int n, int top, int d,
     }
 }
 
+// The kernel's dynamic LDS limit, a property of the function on a device that
+// all builds share: set once, to the most that any build asks for.  (Set per
+// launch to that launch's size, a smaller build of another thread could lower
+// it between a larger one's call and its launch.)
+template <int DP, int NW>
+hipError_t raise_lds_limit() {
+    static std::atomic<uint64_t> done{0};  // one bit per device
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return e;
+    const uint64_t bit = dev >= 0 && dev < 64 ? uint64_t(1) << dev : 0u;
+    if (done.load(std::memory_order_acquire) & bit) return hipSuccess;
+    e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_seg_build<DP, NW>),
+                            hipFuncAttributeMaxDynamicSharedMemorySize, kSegLds);
+    if (e == hipSuccess) done.fetch_or(bit, std::memory_order_release);
+    return e;
+}
+
 template <int DP>
 knn_status build_impl(const float *points, int64_t n, int d, int leaf, hipStream_t s,
                       knn_tree *t, int *flag, hipEvent_t done) {
@@ -1505,9 +1525,8 @@ knn_status build_impl(const float *points, int64_t n, int d, int leaf, hipStream
         a.l1 = l1;
         a.cap = (cmax(l0) + 31) & ~31;
         const size_t lds = decltype(cfg)::bytes(d, a.cap);
-        // (raises the kernel's dynamic LDS limit; a property of the function)
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, int(lds));
+        if (lds > size_t(kSegLds)) return hipErrorInvalidValue;
+        hipError_t e = raise_lds_limit<DP, decltype(cfg)::waves>();
         if (e != hipSuccess) return e;
         kernel<<<1 << l0, 64 * waves, lds, s>>>(a);
         return hipGetLastError();
