@@ -493,6 +493,13 @@ knn_status knn_debug_search_log(const knn_tree *ref, const knn_tree *query, int3
                                 int64_t capacity, int64_t *n_records, int64_t *idx_out,
                                 float *dist_out, void *stream);
 
+/* Makes one device allocation of the calling thread fail as if no memory were
+ * left: the next one for after = 0, the one after it for 1, and so on; a
+ * negative value takes the request back.  Returns what was set before (-1:
+ * nothing, or the failure has happened).  For tests of what a call does without
+ * its scratch. */
+int32_t knn_debug_fail_alloc(int32_t after);
+
 #ifdef __cplusplus
 }
 #endif

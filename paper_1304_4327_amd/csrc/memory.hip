@@ -83,8 +83,12 @@ hipError_t drain_device(Cache &c, int dev) {
 
 }  // namespace
 
+// allocations of this thread until one is made to fail (knn_debug_fail_alloc)
+static thread_local int32_t fail_after = -1;
+
 hipError_t dev_alloc(void **out, size_t bytes, hipStream_t s) {
     *out = nullptr;
+    if (fail_after >= 0 && fail_after-- == 0) return hipErrorOutOfMemory;
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return e;
@@ -188,3 +192,9 @@ size_t cached_bytes() {
 }
 
 }  // namespace knnx
+
+extern "C" int32_t knn_debug_fail_alloc(int32_t after) {
+    const int32_t was = knnx::fail_after;
+    knnx::fail_after = after < 0 ? -1 : after;
+    return was;
+}

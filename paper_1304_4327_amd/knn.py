@@ -125,6 +125,7 @@ _SIGS = {
                                              _P, _P, ctypes.POINTER(ctypes.c_float),
                                              ctypes.POINTER(ctypes.c_float),
                                              ctypes.POINTER(ctypes.c_int64), _P]),
+    "knn_debug_fail_alloc": (ctypes.c_int32, [ctypes.c_int32]),
     "knn_debug_bf16_tiles": (ctypes.c_int, [_P, _P, _P, ctypes.c_int64, ctypes.c_int32, _P, _P,
                                             _P, _P]),
 }
