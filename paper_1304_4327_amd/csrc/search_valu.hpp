@@ -533,6 +533,9 @@ __device__ __forceinline__ void search_valu_body(const SearchArgs &a) {
         const float *rp = a.rlpts + int64_t(node - a.r_first_leaf) * a.r_leaf_slots * DP;
         n_pairs += uint64_t(cnt) * uint64_t(n_valid);
         if constexpr (MT) {
+            // an empty leaf (trees of leaf size 1) has no row to repeat below: its
+            // slots hold FLT_MAX, whose products are no numbers
+            if (cnt == 0) return;
             // the rows that may enter a list, one bit each, by the products or by
             // the FP32 filter of the plain form: beyond the margin's range
             // (coordinates some 1e18 apart, or all within 1e-15), on top of the
