@@ -175,8 +175,10 @@ __device__ __forceinline__ void search_valu_body(const SearchArgs &a) {
     const int2 qr = has_leaf ? a.qrange[qnode] : make_int2(0, 0);
     bool valid0 = has_leaf && li < qr.y;  // this lane holds a query point
     if constexpr (SPLIT) {  // ... of this wave's part of the slot
+        // (an undivided slot goes on without a query: its leaves may be empty,
+        // and their k-th distances are wanted too)
         valid0 = valid0 && in_part<LG>(lane, part, a.split);
-        if (!ballot(valid0)) return;
+        if (a.split && !ballot(valid0)) return;
     }
     bool valid = valid0;  // ... that the current pass searches
     const int qpos = qr.x + li;

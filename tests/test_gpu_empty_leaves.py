@@ -43,3 +43,30 @@ def test_bf16(bound, n_ref, n_q, q_leaf, d, k):
 @pytest.mark.parametrize("d,k", [(5, 4), (8, 10), (13, 16)])
 def test_fp32(bound, n_ref, d, k):
     _run(n_ref, 500, d, k, 1, 32, bound, stats=True)
+
+
+# the largest k-th distance of an empty query leaf is 0, in every kernel that
+# serves the call
+@pytest.mark.parametrize("d,precision", [(3, "fp32"), (8, "fp32"), (16, "fp32"), (16, "bf16"), (24, "fp32"),
+                                         (24, "bf16"), (64, "fp32"), (64, "bf16")])
+@pytest.mark.parametrize("n_ref,n_q", [(300, 70), (4000, 900)])
+def test_kth_distance_of_an_empty_query_leaf(d, precision, n_ref, n_q):
+    import torch
+    from paper_1304_4327_amd import knn
+    print(f"empty query leaves: {n_ref}x{n_q} d={d} {precision}", flush=True)
+    rng = np.random.default_rng(d)
+    ref = rng.standard_normal((n_ref, d)).astype(np.float32)
+    q = rng.standard_normal((n_q, d)).astype(np.float32)
+    rt = knn.knn_build_tree(torch.from_numpy(ref).cuda(), 32)
+    qt = knn.knn_build_tree(torch.from_numpy(q).cuda(), 1)
+    a = knn.tree_arrays(qt)
+    first = a["info"]["first_leaf"]
+    count, start = a["count"][first:], a["start"][first:]
+    assert (count == 0).any() and count.max() == 1
+    kth = torch.full((len(count),), -1.0, device="cuda")
+    _, x, _ = knn.knn_search(rt, qt, 5, precision=precision, leaf_kth_out=kth)
+    torch.cuda.synchronize()
+    x, kth = x.cpu().numpy(), kth.cpu().numpy()
+    assert np.all(kth[count == 0] == 0.0)
+    rows = a["perm"][start[count == 1]]
+    np.testing.assert_array_equal(kth[count == 1], x[rows, 4])
