@@ -101,3 +101,14 @@ def test_small_coordinates(d, scale):
         n = 200 if mixed else 400
         assert np.array_equal(got[0][:n].cpu(), want[0][:n].cpu())
         check_oracle(q, ref, 10, got[0], got[1])
+
+
+# more blocks than the sweep sorts (it goes outward in tree order then)
+@pytest.mark.parametrize("far_ref,far_q", [((), ()), ((1e25, -1e30), (1e25,))])
+@pytest.mark.parametrize("d", [20, 64])
+def test_blocks_in_tree_order(d, far_ref, far_q):
+    print(f"sweep unsorted d={d} {far_ref} {far_q}", flush=True)
+    ref, q = far_sets(70_000, 200, d, far_ref, far_q)
+    got, want = _both(ref, q, 10, 1)
+    assert np.array_equal(got[0].cpu(), want[0].cpu()) and np.array_equal(got[1].cpu(), want[1].cpu())
+    check_oracle(q, ref, 10, got[0], got[1])
