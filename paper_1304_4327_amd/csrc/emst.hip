@@ -352,17 +352,15 @@ __global__ void k_near_lists(const float *pts, const int32_t *perm, const int32_
 #pragma unroll
     for (int j = 0; j < kNear; ++j) {
         // (the search leaves an entry at -1 where fewer than kNear other points
-        // are within FP32's range of this one; last is +inf then, and lim 0)
+        // are within FP32's range of this one; last is +inf then, and lim 0, so
+        // whatever point 0 gives is not listed.  No branch: the lookups of all
+        // entries are in flight together)
         id[j] = int(idx[row + j]);
-        pos[j] = -1;
-        x[j] = __builtin_inf();
-        if (id[j] >= 0) {
-            const int p = inv[id[j]];
-            const double v = d2_fp64_unfused<DP>(q, pts + int64_t(p) * DP);
-            if (v < double(lim)) {
-                x[j] = v;
-                pos[j] = p;
-            }
+        pos[j] = inv[max(id[j], 0)];
+        x[j] = d2_fp64_unfused<DP>(q, pts + int64_t(pos[j]) * DP);
+        if (!(x[j] < double(lim))) {
+            x[j] = __builtin_inf();
+            pos[j] = -1;
         }
     }
     // odd-even transposition: kNear rounds sort kNear entries

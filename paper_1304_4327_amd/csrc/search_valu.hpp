@@ -637,7 +637,7 @@ __device__ __forceinline__ void search_valu_body(const SearchArgs &a) {
                     loose = fp32 ? loose + 1 : max(loose - 4, 0);
                 }
             }
-            if (fp32) {
+            if (__builtin_expect(fp32, 0)) {
                 const uint32_t rows = near_rows(rp, cnt);
                 if (!ballot(rows != 0)) return;
                 mask &= a.walk_ties ? rows : half_bits(rows, hh) | (half_bits(rows, 1 - hh) << 16);
