@@ -632,8 +632,10 @@ __device__ __forceinline__ void search_valu_body(const SearchArgs &a) {
                     // the gap between two clusters lie far from their centre, and
                     // all of a tile's rows may pass for them (one round each below;
                     // the FP32 filter costs as much as eight)
-                    fp32 = ballot(__popc(mask) > 10 &&
-                                  margin(hh ? qlen1 : qlen0) > 0.25f * fminf(dist[K - 1], bound2)) != 0;
+                    const bool many = __popc(mask) > 10;
+                    if (__builtin_expect(ballot(many) != 0, 0))
+                        fp32 = ballot(many && margin(hh ? qlen1 : qlen0) >
+                                                  0.25f * fminf(dist[K - 1], bound2)) != 0;
                     loose = fp32 ? loose + 1 : max(loose - 4, 0);
                 }
             }
