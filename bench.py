@@ -236,7 +236,8 @@ def combined(args):
     print(f"combined: ideal seed {ceiling['speedup_of_ideal_seed']:.3f}x", file=sys.stderr,
           flush=True)
     line = {"workload": name, "n_ref": len(ref), "n_query": nq, "d": ref.shape[1], "k": k,
-            "baseline": "plain FP32 dual-tree traversal, bound B",
+            "baseline": "FP32 search without a seed, bound B (at d > 16 the sweep with "
+                        "BF16 filter tiles and FP64 re-scores)",
             "speedup_learned_bf16_vs_plain_fp32":
                 res["plain_fp32"]["ms_per_step"] / res["learned_bf16"]["ms_per_step"],
             "speedup_plain_bf16_vs_plain_fp32":
@@ -468,29 +469,38 @@ def main():
     if args.compare:
         base_total, base_stats = timed("fp32", max(1, min(args.steps, 2)), 1)
         base_ms = base_total / max(1, min(args.steps, 2)) * 1e3
-        compare = {"baseline": "plain FP32 dual-tree (same workload, same bound)",
+        compare = {"baseline": "FP32 search without a seed (same workload, same bound)",
                    "baseline_ms_per_step": base_ms, "variant_ms_per_step": ms_step,
                    "speedup": base_ms / ms_step,
                    "baseline_pairs_per_query": float(np.mean([s["pairs"] for s in base_stats])) / nq}
 
     kern_ms = float(np.mean([s["ms_main_kernel"] for s in stats]))
     pairs = float(np.mean([s["pairs"] for s in stats]))
-    if args.precision == "bf16":
-        # BF16 MFMA: 2 d flops per pair on the matrix cores (padded k-steps
-        # of 16 count as issued work, the algorithmic count uses d)
-        flop_per_pair = 2 * d
-        peak = PEAKS["bf16_mfma_tflops"]
-        # the BF16 kernel the library picks: the leaf sweep at stride 64,
-        # the traversal kernel with matrix-core tiles at stride 16 / 32 with
-        # lists of <= 16, else the per-leaf MFMA kernel
-        stride = 16 if d <= 16 else 32 if d <= 32 else 64
-        bound_kind = "mfma"
-        kname = ("k_search_mfma_sweep" if stride == 64 else
-                 "k_search_valu_mt" if k + (1 if self_mode else 0) <= 16 else "k_search_mfma")
-    else:
+    # the kernel the library picks (api.hip): the sweep with two query leaves
+    # per wave at stride 64, and for FP32 at stride 32 from 3000 references; the
+    # walk with matrix-core tiles for BF16 at stride 16 / 32 and for FP32 at
+    # stride 8 / 16 from 2048 references, lists of <= 16; else the per-leaf BF16
+    # kernel or the FP32 walk.  A seeded FP32 search stays in the walk.
+    stride = next(x for x in (4, 8, 16, 32, 64) if d <= x)
+    short = k + (1 if self_mode else 0) <= 16
+    bf16 = args.precision == "bf16"
+    pairs_of_leaves = leaf <= 32 and (stride == 64 if bf16 else
+                                      stride >= 32 and not args.learned and len(ref) >= 3000)
+    tiles = short and (stride in (16, 32) if bf16 else
+                       stride in (8, 16) and 16 < leaf <= 32 and not args.learned
+                       and len(ref) >= 2048)
+    kname = ("k_search_pair" if pairs_of_leaves else "k_search_valu_mt" if tiles else
+             "k_search_mfma" if bf16 else "k_search_valu")
+    if kname == "k_search_valu":
         flop_per_pair = 3 * d - 1
         peak = PEAKS["fp32_vector_tflops"]
-        bound_kind, kname = "alu", "k_search_valu"
+        bound_kind = "alu"
+    else:
+        # pairs on the matrix cores: 2 d flops each (padded k-steps of 16 count
+        # as issued work, the algorithmic count uses d)
+        flop_per_pair = 2 * d
+        peak = PEAKS["bf16_mfma_tflops"]
+        bound_kind = "mfma"
     achieved = pairs * flop_per_pair / (kern_ms * 1e-3) / 1e12
     traffic = None if args.learned else TRAFFIC_BYTES_PER_LAUNCH.get((args.workload, args.precision))
     line = {

@@ -107,7 +107,14 @@ typedef struct knn_opts {
     float *leaf_kth_out;        /* device, one per query leaf, or NULL: largest
                                    final k-th distance in the leaf (the final
                                    B1 of the leaf)                                 */
-    knn_stats *stats;           /* host, or NULL                                   */
+    knn_stats *stats;           /* host, or NULL.  Counters describe whole query
+                                   leaves: at d <= 16 a call that asks for them (or
+                                   for leaf_kth_out) is served by the kernel that
+                                   walks a group of query leaves per wavefront, also
+                                   where few queries would otherwise take a faster
+                                   one (one query per wavefront); same answer, up to
+                                   some twenty times the time, and the counters and
+                                   times are that kernel's                         */
 } knn_opts;
 
 /* Fill *opts with the defaults: bound B, FP32, no self exclusion, no seed. */
@@ -200,11 +207,16 @@ knn_status knn_search(const knn_tree *ref, const knn_tree *query, int32_t k,
 
 /* knn_search for callers that cannot allocate device memory (code under
  * graph capture, tight serving loops, harnesses that forbid allocation): the
- * same search, kernels and answer as knn_search on trees built beforehand,
- * with the per-call scratch (launch order, counters, fallback flags and
+ * same search and answer as knn_search on trees built beforehand (where more
+ * points tie with the k-th distance than a kernel's lists have spare entries,
+ * another of them may be returned), with the per-call scratch (launch order, counters, fallback flags and
  * bounds) in a fixed 4 MiB device array that the library holds on every
  * device it runs on until the process ends.  It calls no device allocation
- * or free and records no memset node (clears are kernels).  Limits: query
+ * or free and records no memset node (clears are kernels).  The kernels are
+ * knn_search's but for d > 32, and FP32 requests at d > 16: there knn_search
+ * allocates operands for a faster sweep, which this entry does without (FP32
+ * at 20,000 queries of 100,000 points, d = 64: about fourteen times the time).
+ * Limits: query
  * trees of up to 2^18 leaves always fit; a larger tree whose scratch
  * (12 bytes per query leaf with a seed, 4 per wavefront of leaves without)
  * exceeds the array is rejected with KNN_E_INVALID_ARG before any device

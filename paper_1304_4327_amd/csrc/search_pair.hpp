@@ -731,7 +731,11 @@ k_search_pair(const SearchArgs a) {
     }
 }
 
-// list lengths: the smallest that holds kk + 2 entries (kk <= 64)
+// list lengths: the smallest that holds kk + 2 entries (kk <= 64).  They hold k =
+// 8, 16, 32, 50 and 64 (or that many with the query's own point: 53 = 51 + 2); a
+// list costs two registers an entry, and 53 is the longest of them that leaves
+// room for two waves per SIMD (256 registers, some 75 in scratch); 66 has one
+// wave per SIMD and nothing in scratch.
 template <int DP>
 hipError_t launch_search_pair(const SearchArgs &a, int kk, int grid, hipStream_t s) {
     if (!a.sw_abf || a.r_leaf_slots > 32) return hipErrorInvalidValue;

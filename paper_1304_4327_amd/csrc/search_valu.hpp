@@ -62,7 +62,9 @@
 // l % 32 of half l / 32 of the products, so it holds the bits of half of its
 // own query's 32 rows and takes the other half's from lane l ^ 32.  A row is a
 // candidate when its value minus the proven margin beats min(D_p[k], B); so
-// the lists are those of the plain form, for either precision request.
+// the lists are those of the plain form, for either precision request.  Where
+// the margin does not hold (lengths near FP32's limits) or lets most rows
+// through, the plain form's FP32 filter joins the products or replaces them.
 //
 // What bounds it: instruction issue.  The plain form spends about 2 d + 2
 // instructions on every reference point of a tile (600 a tile at d = 8), the
