@@ -502,32 +502,36 @@ __device__ __forceinline__ void search_valu_body(const SearchArgs &a) {
     // a wave that has its SIMD to itself waits for each (200,000 by 200,000
     // points of a crowded mixture, d = 16, k = 10: 25.2 ms so, 16.6 here)
     auto near_rows = [&](const float *rp, int cnt) __attribute__((always_inline)) -> uint32_t {
-        const float lim = fminf(dist[K - 1], bound2 * kSlack);
-        const float thr = valid ? (RESCORE ? lim * kGamma : lim) : -kInf;
-        uint32_t rows = 0;
-        constexpr int H = D / 2;  // dimensions of a lane: row jj, half hh
-        float x[H];
-        {
-            const float *row = rp + (jj < cnt ? jj : 0) * DP + hh * H;
+        if constexpr (!MT) {
+            return 0;  // (rows of one dimension have no halves)
+        } else {
+            const float lim = fminf(dist[K - 1], bound2 * kSlack);
+            const float thr = valid ? (RESCORE ? lim * kGamma : lim) : -kInf;
+            uint32_t rows = 0;
+            constexpr int H = D / 2;  // dimensions of a lane: row jj, half hh
+            float x[H];
+            {
+                const float *row = rp + (jj < cnt ? jj : 0) * DP + hh * H;
 #pragma unroll
-            for (int u = 0; u < H; u += 4) {
-                const float4 v = *reinterpret_cast<const float4 *>(row + u);
-                x[u] = v.x, x[u + 1] = v.y, x[u + 2] = v.z, x[u + 3] = v.w;
+                for (int u = 0; u < H; u += 4) {
+                    const float4 v = *reinterpret_cast<const float4 *>(row + u);
+                    x[u] = v.x, x[u + 1] = v.y, x[u + 2] = v.z, x[u + 3] = v.w;
+                }
             }
-        }
 #pragma unroll 2
-        for (int t = 0; t < cnt; ++t) {  // (the same sums as the plain form's)
-            float sd = 0.f;
+            for (int t = 0; t < cnt; ++t) {  // (the same sums as the plain form's)
+                float sd = 0.f;
 #pragma unroll
-            for (int j = 0; j < D; ++j) {
-                const float r = __builtin_bit_cast(
-                    float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x[j % H]), t + 32 * (j / H)));
-                const float df = q[j] - r;
-                sd = fmaf(df, df, sd);
+                for (int j = 0; j < D; ++j) {
+                    const float r = __builtin_bit_cast(
+                        float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x[j % H]), t + 32 * (j / H)));
+                    const float df = q[j] - r;
+                    sd = fmaf(df, df, sd);
+                }
+                rows |= uint32_t(sd < thr) << t;
             }
-            rows |= uint32_t(sd < thr) << t;
+            return rows;
         }
-        return rows;
     };
     auto tile = [&](int node) {
         ++n_tiles;
