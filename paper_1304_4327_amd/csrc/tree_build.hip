@@ -717,9 +717,9 @@ struct SegCfg {
 // waves of the workgroup that splits a segment down to kSmallSeg points.  Up to
 // 16 dimensions 16 waves reach 7936 points in LDS where 8 reach 3968 (us with 16 and
 // with 8, d = 3: 5000 points 137 and 167, 1.5M 720 and 740; 2000 points, where
-// one level fewer is shared, 110 and 102).  Longer rows are read in place: 16
-// waves there gain at 2000 to 12,000 points (5000 at d = 32 336 and 241) and lose
-// at 400,000 (d = 24 930 and 948).
+// one level fewer is shared, 110 and 102).  Longer rows are read in place, and
+// there 16 waves gain up to 100,000 points (d = 32: 5000 points 241 and 336,
+// 100,000 596 and 621) and lose 2% at 400,000 (d = 24: 948 and 930).
 constexpr int mid_waves(int DP) { return DP <= 16 ? 16 : 8; }
 constexpr int kEndWaves = 4;  // of the one that finishes it
 
